@@ -74,65 +74,78 @@ __global__ __launch_bounds__(256) void hessian_kernel(const float* __restrict__ 
     }
 }
 
-// Cholesky factorization of diagonal tile k (its trailing updates from the
-// tiles left of it are already applied).  A non-positive pivot records its
-// 1-based column in *info (first failure wins) and continues with pivot 1.
-__global__ __launch_bounds__(256) void potrf_diag_kernel(double* __restrict__ A, int n, int k,
-                                                         int32_t* __restrict__ info) {
-  __shared__ double a[FT][FT + 1];
-  const size_t base = (size_t)k * FT;
-  for (int idx = threadIdx.x; idx < FT * FT; idx += 256) {
-    const int r = idx / FT, c = idx % FT;
-    a[r][c] = c <= r ? A[(base + r) * n + base + c] : 0.0;
-  }
-  __syncthreads();
-  for (int j = 0; j < FT; ++j) {
-    if (threadIdx.x == 0) {
-      double d = a[j][j];
-      if (!(d > 0.0)) {
-        atomicCAS(info, 0, (int32_t)(base + j + 1));
-        d = 1.0;
-      }
-      a[j][j] = sqrt(d);
-    }
-    __syncthreads();
-    const double djj = a[j][j];
-    for (int r = j + 1 + (int)threadIdx.x; r < FT; r += 256) a[r][j] = a[r][j] / djj;
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < FT * FT; idx += 256) {
-      const int r = idx / FT, c = idx % FT;
-      if (c > j && r >= c) a[r][c] = fma(-a[r][j], a[c][j], a[r][c]);
-    }
-    __syncthreads();
-  }
-  for (int idx = threadIdx.x; idx < FT * FT; idx += 256) {
-    const int r = idx / FT, c = idx % FT;
-    A[(base + r) * n + base + c] = c <= r ? a[r][c] : 0.0;
-  }
+__device__ inline double lane_value(double v, int lane) {
+  const uint64_t u = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// Panel tiles below diagonal tile k: A[i][k] <- A[i][k] L_kk^-T (one lane
-// per tile row, forward substitution in ascending column order).
-__global__ __launch_bounds__(64) void trsm_kernel(double* __restrict__ A, int n, int k) {
-  __shared__ double l[FT][FT + 1], b[FT][FT + 1];
-  const size_t bk = (size_t)k * FT, bi = (size_t)(k + 1 + blockIdx.x) * FT;
-  for (int idx = threadIdx.x; idx < FT * FT; idx += 64) {
-    const int r = idx / FT, c = idx % FT;
-    l[r][c] = A[(bk + r) * n + bk + c];
-    b[r][c] = A[(bi + r) * n + bk + c];
-  }
-  __syncthreads();
+// Cholesky factorization of diagonal tile k (its trailing updates from the
+// tiles left of it are already applied) by one wave: lane r holds row r in
+// registers, column j's multipliers come from their lanes, so no step waits on
+// LDS or a barrier: 57 us a tile, 88 us as 64 steps of
+// three barriers by a 256-thread workgroup.  A
+// non-positive pivot records its 1-based column in *info (first failure wins)
+// and continues with pivot 1.
+__global__ __launch_bounds__(64) void potrf_diag_kernel(double* __restrict__ A, int n, int k,
+                                                        int32_t* __restrict__ info) {
+  __shared__ double a[FT][FT + 1];
+  const size_t base = (size_t)k * FT;
   const int r = threadIdx.x;
+#pragma unroll 8
+  for (int i = 0; i < FT; ++i) a[i][r] = A[(base + i) * n + base + r];
+  __syncthreads();
+  double v[FT];
+#pragma unroll
+  for (int c = 0; c < FT; ++c) v[c] = a[r][c];
+#pragma unroll
   for (int j = 0; j < FT; ++j) {
-    double v = b[r][j];
-    for (int m = 0; m < j; ++m) v = fma(-b[r][m], l[j][m], v);
-    b[r][j] = v / l[j][j];
+    double d = lane_value(v[j], j);
+    if (!(d > 0.0)) {
+      if (r == 0) atomicCAS(info, 0, (int32_t)(base + j + 1));
+      d = 1.0;
+    }
+    d = sqrt(d);
+    v[j] = r == j ? d : v[j] / d;  // rows above the diagonal are not stored
+#pragma unroll
+    for (int c = j + 1; c < FT; ++c) v[c] = fma(-v[j], lane_value(v[j], c), v[c]);
+  }
+#pragma unroll
+  for (int c = 0; c < FT; ++c) a[r][c] = c <= r ? v[c] : 0.0;
+  __syncthreads();
+#pragma unroll 8
+  for (int i = 0; i < FT; ++i) A[(base + i) * n + base + r] = a[i][r];
+}
+
+// Panel tiles below diagonal tile k: A[i][k] <- A[i][k] L_kk^-T.  One lane
+// per tile row, held in registers; each solved column is taken off the later
+// ones at once (every element still sees its terms in ascending column order).
+__global__ __launch_bounds__(64) void trsm_kernel(double* __restrict__ A, int n, int k) {
+  __shared__ __attribute__((aligned(16))) double lt[FT][FT + 2];  // lt[j][m] = L[m][j]
+  __shared__ double b[FT][FT + 1];
+  const size_t bk = (size_t)k * FT, bi = (size_t)(k + 1 + blockIdx.x) * FT;
+  const int r = threadIdx.x;
+#pragma unroll 8
+  for (int i = 0; i < FT; ++i) {
+    lt[r][i] = A[(bk + i) * n + bk + r];
+    b[i][r] = A[(bi + i) * n + bk + r];
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < FT * FT; idx += 64) {
-    const int rr = idx / FT, c = idx % FT;
-    A[(bi + rr) * n + bk + c] = b[rr][c];
+  double v[FT];
+#pragma unroll
+  for (int c = 0; c < FT; ++c) v[c] = b[r][c];
+#pragma unroll
+  for (int j = 0; j < FT; ++j) {
+    v[j] = v[j] / lt[j][j];
+#pragma unroll
+    for (int m = j + 1; m < FT; ++m) v[m] = fma(-v[j], lt[j][m], v[m]);
   }
+#pragma unroll
+  for (int c = 0; c < FT; ++c) b[r][c] = v[c];
+  __syncthreads();
+#pragma unroll 8
+  for (int i = 0; i < FT; ++i) A[(bi + i) * n + bk + r] = b[i][r];
 }
 
 // Trailing update of the lower tiles (i, j), k < j <= i:
@@ -198,27 +211,33 @@ __global__ __launch_bounds__(64) void trinv_diag_kernel(const double* __restrict
   }
 }
 
-// Block row i of M = L^-1 below the diagonal: for tile column k < i
-// (workgroup k), M[i][k] = -M_ii (sum_{m=k}^{i-1} L[i][m] M[m][k]).
-__global__ __launch_bounds__(256) void trinv_row_kernel(const double* __restrict__ L,
-                                                        double* __restrict__ M, int n, int i) {
-  const int k = blockIdx.x;
+// M = L^-1 below the diagonal, M[i][k] = -M_ii (sum_{m=k}^{i-1} L[i][m] M[m][k]).
+// Step m adds term m to the sums of every tile (i, k), k <= m < i, kept in M's
+// own tiles, and finishes block row m + 1, whose sums are then complete: the
+// terms of an element are added in ascending m as before, but one step is
+// m + 1 columns of n/64 - m - 1 tiles in parallel instead of one serial row
+// (n = 2048: 31 launches of
+// 19 us, 163 us as rows).
+__global__ __launch_bounds__(256) void trinv_step_kernel(const double* __restrict__ L,
+                                                         double* __restrict__ M, int n, int m) {
+  const int k = blockIdx.x, i = m + 1 + blockIdx.y;
   __shared__ double pa[FT][FT + 1], pb[FT][FT + 1];
   const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  const size_t bi = (size_t)i * FT, bk = (size_t)k * FT;
+  const size_t bi = (size_t)i * FT, bk = (size_t)k * FT, bm = (size_t)m * FT;
   double acc[4][4];
 #pragma unroll
   for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) acc[r][c] = 0.0;
-  for (int m = k; m < i; ++m) {
-    const size_t bm = (size_t)m * FT;
-    for (int idx = threadIdx.x; idx < FT * FT; idx += 256) {
-      const int r = idx / FT, c = idx % FT;
-      pa[r][c] = L[(bi + r) * n + bm + c];
-      pb[r][c] = M[(bm + r) * n + bk + c];
-    }
-    __syncthreads();
+    for (int c = 0; c < 4; ++c) acc[r][c] = k < m ? M[(bi + ty * 4 + r) * n + bk + tx * 4 + c] : 0.0;
+  auto load = [&](const double* A, size_t row, size_t col, double (&t)[FT][FT + 1]) {
+    double v[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) v[q] = A[(row + threadIdx.x / FT + 4 * q) * n + col + threadIdx.x % FT];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) t[threadIdx.x / FT + 4 * q][threadIdx.x % FT] = v[q];
+  };
+  auto product = [&] {  // acc += pa pb
+#pragma unroll 4
     for (int q = 0; q < FT; ++q) {
       double a[4], b[4];
 #pragma unroll
@@ -230,37 +249,32 @@ __global__ __launch_bounds__(256) void trinv_row_kernel(const double* __restrict
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[r][c] = fma(a[r], b[c], acc[r][c]);
     }
-    __syncthreads();
-  }
-  // T in pb, M_ii in pa; then M[i][k] = -M_ii T
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) pb[ty * 4 + r][tx * 4 + c] = acc[r][c];
-  for (int idx = threadIdx.x; idx < FT * FT; idx += 256) {
-    const int r = idx / FT, c = idx % FT;
-    pa[r][c] = M[(bi + r) * n + bi + c];
-  }
+  };
+  load(L, bi, bm, pa);
+  load(M, bm, bk, pb);
   __syncthreads();
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[r][c] = 0.0;
-  for (int q = 0; q < FT; ++q) {
-    double a[4], b[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) a[r] = pa[ty * 4 + r][q];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) b[c] = pb[q][tx * 4 + c];
+  product();
+  if (i == m + 1) {  // workgroup-uniform: the sums of this block row are complete
+    __syncthreads();
+    load(M, bi, bi, pa);
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) acc[r][c] = fma(a[r], b[c], acc[r][c]);
+      for (int c = 0; c < 4; ++c) {
+        pb[ty * 4 + r][tx * 4 + c] = acc[r][c];
+        acc[r][c] = 0.0;
+      }
+    __syncthreads();
+    product();
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[r][c] = -acc[r][c];
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) M[(bi + ty * 4 + r) * n + bk + tx * 4 + c] = -acc[r][c];
+    for (int c = 0; c < 4; ++c) M[(bi + ty * 4 + r) * n + bk + tx * 4 + c] = acc[r][c];
 }
 
 // U[a][b] = M[n-1-a][n-1-b] rounded to binary32 on and above the diagonal.
@@ -280,148 +294,257 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const float* __restrict_
   if (i < count) dst[i] = src[i];
 }
 
-constexpr int kMaxGamma = 128;  // compensation block size: 64 or 128 columns
-
-// One lane per row: quantize block [b0, b0 + gamma) of level `lev` from the
-// row's current targets T, write its codes into the packed layout, update
-// the row's residual chain R, and solve E = D U_BB^-1 for its block error D.
-//   W: the expert's original rows [N][h]; T, R: [N][h]; E: [N][gamma].
-template <int G>
-__global__ __launch_bounds__(64) void calib_quant_kernel(
+// Quantize block [b0, b0 + GAMMA) of level `lev` from the rows' current
+// targets T, write the codes into the packed layout, update the rows' residual
+// chains R, and solve E = D U_BB^-1 for their block errors D.
+//   W: the expert's original rows [N][h]; T, R: [N][h]; E: [N][GAMMA].
+// A wave takes kQuantRows rows with lane l holding columns l, l + 64 of each: a
+// ballot is two plane words, and the solve takes column j's error (a lane
+// broadcast, one division for all rows) off the later columns of every lane,
+// U's row from LDS, so a column costs one step instead of j dependent ones.
+// Every element still sees its terms in ascending column order.  Only the sum
+// of magnitudes is one chain per (row, group), run by a lane each from LDS.
+// 2816 x 2048, blocks of 128: 26 us a launch, 228 us with one lane per row.
+constexpr int kQuantRows = 4, kQuantWaves = 4;
+template <int G, int GAMMA>
+__global__ __launch_bounds__(64 * kQuantWaves) void calib_quant_kernel(
     const float* __restrict__ W, const float* __restrict__ T, float* __restrict__ R,
     const float* __restrict__ U, float* __restrict__ E, MwqView m, uint32_t* __restrict__ planes,
-    uint16_t* __restrict__ scales, uint8_t* __restrict__ zeros, int e, int lev, int b0,
-    int gamma) {
-  __shared__ float de[kMaxGamma * 64];  // lane-private columns: de[j * 64 + lane]
-  const int lane = threadIdx.x;
-  const int n = blockIdx.x * 64 + lane;
-  if (n >= m.rows) return;  // no barrier below: the LDS columns are lane-private
-  const int h = m.cols, BR = 2048 / G;
-  const int rb = n / BR, i = n % BR;
+    uint16_t* __restrict__ scales, uint8_t* __restrict__ zeros, int e, int lev, int b0) {
+  constexpr int C = GAMMA / 64, NG = GAMMA / G;  // columns per lane, groups per block
+  constexpr int CG = G / 64;                     // lane columns per group
+  constexpr int BR = 2048 / G;
+  __shared__ float us[GAMMA][GAMMA];
+  __shared__ __attribute__((aligned(16))) float mag[kQuantWaves][kQuantRows][GAMMA + 4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n0 = (blockIdx.x * kQuantWaves + wave) * kQuantRows;
+  const int h = m.cols;
   const int qmax = (1 << m.b_min) - 1;
-  const float* t = T + (size_t)n * h;
-  const float* w = W + (size_t)n * h;
-  float* rr = R + (size_t)n * h;
-  for (int c0 = b0; c0 < b0 + gamma; c0 += G) {
-    const int kb = c0 / G;
-    const size_t blk = m.block(e, rb, kb);
-    if (lev == 0) {
-      float mn = 0.0f, mx = 0.0f;
-      for (int k = 0; k < G; ++k) {
-        const float v = t[c0 + k];
-        if (v < mn) mn = v;
-        if (v > mx) mx = v;
-      }
-      const float range = mx - mn;
-      uint16_t s_h = f2h(range / (float)qmax);
-      float s1 = h2f(s_h);
-      if (!(s1 > 0.0f) || __builtin_isinf(s1)) {
-        s_h = 0x3c00u;
-        s1 = 1.0f;
-      }
-      float zf = rintf(-mn / s1);
-      zf = zf < 0.0f ? 0.0f : zf;
-      zf = zf > (float)qmax ? (float)qmax : zf;
-      const int z = (int)zf;
-      zeros[m.zero_idx(blk, i)] = (uint8_t)z;
-      scales[m.scale_idx(blk, 0, i)] = s_h;
-      for (int sub = 0; sub < G / 32; ++sub) {
-        uint32_t words[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int j = 0; j < 32; ++j) {
-          const int k = c0 + sub * 32 + j;
-          const float v = t[k];
-          float qf = rintf(v / s1 + (float)z);
+
+  float t[kQuantRows][C], w[kQuantRows][C];  // targets; W (level 0) or the residual chain
+#pragma unroll
+  for (int r = 0; r < kQuantRows; ++r)
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const size_t at = (size_t)(n0 + r) * h + b0 + 64 * c + lane;
+      const bool ok = n0 + r < m.rows;
+      t[r][c] = ok ? T[at] : 0.0f;
+      w[r][c] = ok ? (lev == 0 ? W[at] : R[at]) : 0.0f;
+    }
+#pragma unroll 8
+  for (int idx = threadIdx.x; idx < GAMMA * GAMMA; idx += 64 * kQuantWaves)
+    us[idx / GAMMA][idx % GAMMA] = U[(size_t)(b0 + idx / GAMMA) * h + b0 + idx % GAMMA];
+
+  float v[kQuantRows][C];  // block errors, then E
+  if (lev == 0) {
+#pragma unroll
+    for (int r = 0; r < kQuantRows; ++r) {
+      const int n = n0 + r;
+      const bool ok = n < m.rows;  // wave-uniform
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        float mn = 0.0f, mx = 0.0f;
+#pragma unroll
+        for (int c = g * CG; c < (g + 1) * CG; ++c) {
+          mn = t[r][c] < mn ? t[r][c] : mn;
+          mx = t[r][c] > mx ? t[r][c] : mx;
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+          const float a = __shfl_xor(mn, off, 64), b = __shfl_xor(mx, off, 64);
+          mn = a < mn ? a : mn;
+          mx = b > mx ? b : mx;
+        }
+        const float range = mx - mn;
+        uint16_t s_h = f2h(range / (float)qmax);
+        float s1 = h2f(s_h);
+        if (!(s1 > 0.0f) || __builtin_isinf(s1)) {
+          s_h = 0x3c00u;
+          s1 = 1.0f;
+        }
+        float zf = rintf(-mn / s1);
+        zf = zf < 0.0f ? 0.0f : zf;
+        zf = zf > (float)qmax ? (float)qmax : zf;
+        const int z = (int)zf;
+        const size_t blk = m.block(e, ok ? n / BR : 0, b0 / G + g);
+        const int i = n % BR;
+        if (ok && lane == 0) {
+          zeros[m.zero_idx(blk, i)] = (uint8_t)z;
+          scales[m.scale_idx(blk, 0, i)] = s_h;
+        }
+#pragma unroll
+        for (int c = g * CG; c < (g + 1) * CG; ++c) {
+          const float x = t[r][c];
+          float qf = rintf(x / s1 + (float)z);
           qf = qf < 0.0f ? 0.0f : qf;
           qf = qf > (float)qmax ? (float)qmax : qf;
           const int q = (int)qf;
           const float what = (float)(q - z) * s1;
-          de[(k - b0) * 64 + lane] = v - what;
-          rr[k] = w[k] - what;
-          for (int p = 0; p < 8; ++p)
-            if (p < m.b_min) words[p] |= (uint32_t)((q >> p) & 1) << j;
+          v[r][c] = x - what;
+          w[r][c] = w[r][c] - what;
+          for (int p = 0; p < m.b_min; ++p) {
+            const uint64_t bits = __ballot((q >> p) & 1);
+            if (ok && lane < 2)
+              planes[m.plane_word(blk, p, (2 * (c - g * CG) + lane) * BR + i)] =
+                  (uint32_t)(lane ? bits >> 32 : bits);
+          }
         }
-        for (int p = 0; p < m.b_min; ++p)
-          planes[m.plane_word(blk, p, sub * BR + i)] = words[p];
       }
-    } else {
-      float acc = 0.0f;
-      for (int k = 0; k < G; ++k) acc = acc + fabsf(t[c0 + k]);
-      const uint16_t sb_h = f2h(acc / (float)G);
-      const float sb = h2f(sb_h);
-      scales[m.scale_idx(blk, lev, i)] = sb_h;
-      const int p = m.b_min + lev - 1;
-      for (int sub = 0; sub < G / 32; ++sub) {
-        uint32_t word = 0;
-        for (int j = 0; j < 32; ++j) {
-          const int k = c0 + sub * 32 + j;
-          const float v = t[k];
-          const bool pos = v >= 0.0f;  // -0.0 >= 0: sign +1
-          word |= (uint32_t)pos << j;
-          de[(k - b0) * 64 + lane] = pos ? (v - sb) : (v + sb);
-          rr[k] = pos ? (rr[k] - sb) : (rr[k] + sb);
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < kQuantRows; ++r)
+#pragma unroll
+      for (int c = 0; c < C; ++c) mag[wave][r][64 * c + lane] = fabsf(t[r][c]);
+    // lane r NG + g sums group g of row r in ascending column order (the
+    // wave's own LDS writes above are ordered before these reads)
+    float acc = 0.0f;
+    if (lane < kQuantRows * NG) {
+      const float4* src = (const float4*)&mag[wave][lane / NG][(lane % NG) * G];
+#pragma unroll 4
+      for (int k = 0; k < G / 4; ++k) {
+        const float4 x = src[k];
+        acc = acc + x.x;
+        acc = acc + x.y;
+        acc = acc + x.z;
+        acc = acc + x.w;
+      }
+    }
+    const uint32_t sb_l = f2h(acc / (float)G);
+#pragma unroll
+    for (int r = 0; r < kQuantRows; ++r) {
+      const int n = n0 + r;
+      const bool ok = n < m.rows;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const uint16_t sb_h = (uint16_t)__builtin_amdgcn_readlane(sb_l, r * NG + g);
+        const float sb = h2f(sb_h);
+        const size_t blk = m.block(e, ok ? n / BR : 0, b0 / G + g);
+        const int i = n % BR, p = m.b_min + lev - 1;
+        if (ok && lane == 0) scales[m.scale_idx(blk, lev, i)] = sb_h;
+#pragma unroll
+        for (int c = g * CG; c < (g + 1) * CG; ++c) {
+          const float x = t[r][c];
+          const bool pos = x >= 0.0f;  // -0.0 >= 0: sign +1
+          const uint64_t bits = __ballot(pos);
+          if (ok && lane < 2)
+            planes[m.plane_word(blk, p, (2 * (c - g * CG) + lane) * BR + i)] =
+                (uint32_t)(lane ? bits >> 32 : bits);
+          v[r][c] = pos ? (x - sb) : (x + sb);
+          w[r][c] = pos ? (w[r][c] - sb) : (w[r][c] + sb);
         }
-        planes[m.plane_word(blk, p, sub * BR + i)] = word;
       }
     }
   }
+#pragma unroll
+  for (int r = 0; r < kQuantRows; ++r)
+    if (n0 + r < m.rows)
+#pragma unroll
+      for (int c = 0; c < C; ++c) R[(size_t)(n0 + r) * h + b0 + 64 * c + lane] = w[r][c];
+  __syncthreads();  // the block of U is in LDS
+
   // E = D U_BB^-1, forward substitution in ascending order
-  for (int j = 0; j < gamma; ++j) {
-    float v = de[j * 64 + lane];
-    for (int q = 0; q < j; ++q)
-      v = fmaf(-de[q * 64 + lane], U[(size_t)(b0 + q) * h + (b0 + j)], v);
-    v = v / U[(size_t)(b0 + j) * h + (b0 + j)];
-    de[j * 64 + lane] = v;
-    E[(size_t)n * gamma + j] = v;
+#pragma unroll
+  for (int cj = 0; cj < C; ++cj) {
+    float un[C], dn = us[64 * cj][64 * cj];
+#pragma unroll
+    for (int c = cj; c < C; ++c) un[c] = us[64 * cj][64 * c + lane];
+    for (int lj = 0; lj < 64; ++lj) {
+      float u[C];
+      const float diag = dn;
+#pragma unroll
+      for (int c = cj; c < C; ++c) u[c] = un[c];
+      const int jn = 64 * cj + min(lj + 1, 63);  // the next row of U is read ahead
+      dn = us[jn][jn];
+#pragma unroll
+      for (int c = cj; c < C; ++c) un[c] = us[jn][64 * c + lane];
+      // the rows' column-j values side by side in lanes 0 .. kQuantRows - 1
+      float x = 0.0f;
+#pragma unroll
+      for (int r = 0; r < kQuantRows; ++r) {
+        const float vj =
+            __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v[r][cj]), lj));
+        x = lane == r ? vj : x;
+      }
+      x = x / diag;
+#pragma unroll
+      for (int r = 0; r < kQuantRows; ++r) {
+        const float ej = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), r));
+        const float upd = fmaf(-ej, u[cj], v[r][cj]);
+        v[r][cj] = lane > lj ? upd : lane == lj ? ej : v[r][cj];
+#pragma unroll
+        for (int c = cj + 1; c < C; ++c) v[r][c] = fmaf(-ej, u[c], v[r][c]);
+      }
+    }
   }
+#pragma unroll
+  for (int r = 0; r < kQuantRows; ++r)
+    if (n0 + r < m.rows)
+#pragma unroll
+      for (int c = 0; c < C; ++c) E[(size_t)(n0 + r) * GAMMA + 64 * c + lane] = v[r][c];
 }
 
 // T[n][f] -= sum_j E[n][j] U[b0 + j][f] for the columns f >= b0 + gamma, as
-// one fmaf chain per element in ascending j.  Tile: 64 rows x 32 columns,
-// 4 x 4 per thread (128 threads).
-constexpr int kUpdCols = 32;
-__global__ __launch_bounds__(128) void calib_update_kernel(float* __restrict__ T,
+// one fmaf chain per element in ascending j.  Tile: 64 rows x 64 columns,
+// 4 x 4 per thread, E transposed in LDS so that a step reads two 16-byte
+// vectors for 16 products; 32 columns of E at a time keep the tile at 16 KB,
+// so that several workgroups share a compute unit.  2816 x 2048: 19 us a
+// launch on average, 82 us with 64 x 32 tiles of 128 threads.
+constexpr int kUpdTile = 64, kUpdDepth = 32;
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // U: 4-byte aligned
+__global__ __launch_bounds__(256) void calib_update_kernel(float* __restrict__ T,
                                                            const float* __restrict__ U,
                                                            const float* __restrict__ E, int N,
                                                            int h, int b0, int gamma) {
-  __shared__ float es[64 * (kMaxGamma + 1)];   // [64][gamma + 1]
-  __shared__ float us[kMaxGamma * kUpdCols];   // [gamma][32]
-  const int n0 = blockIdx.y * 64;
-  const int f0 = b0 + gamma + blockIdx.x * kUpdCols;
-  for (int idx = threadIdx.x; idx < 64 * gamma; idx += 128) {
-    const int r = idx / gamma, j = idx % gamma;
-    es[r * (gamma + 1) + j] = n0 + r < N ? E[(size_t)(n0 + r) * gamma + j] : 0.0f;
-  }
-  for (int idx = threadIdx.x; idx < gamma * kUpdCols; idx += 128) {
-    const int j = idx / kUpdCols, c = idx % kUpdCols;
-    us[j * kUpdCols + c] = U[(size_t)(b0 + j) * h + f0 + c];
-  }
-  __syncthreads();
-  const int tx = threadIdx.x % 8, ty = threadIdx.x / 8;
+  __shared__ __attribute__((aligned(16))) float es[kUpdDepth][kUpdTile + 4];
+  __shared__ __attribute__((aligned(16))) float us[kUpdDepth][kUpdTile];
+  const int n0 = blockIdx.y * kUpdTile;
+  const int f0 = b0 + gamma + blockIdx.x * kUpdTile;
+  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
   float acc[4][4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+  for (int r = 0; r < 4; ++r) {
+    const int n = n0 + ty * 4 + r;
+    const float4 v = n < N ? *(const float4*)(T + (size_t)n * h + f0 + tx * 4)
+                           : float4{0.f, 0.f, 0.f, 0.f};
+    acc[r][0] = v.x; acc[r][1] = v.y; acc[r][2] = v.z; acc[r][3] = v.w;
+  }
+  // this thread's part of a depth step: E row er, columns 4 ej .. and + 16;
+  // U rows uj, uj + 16, columns 4 uc ..
+  const int er = threadIdx.x % 64, ej = threadIdx.x / 64;
+  const int uj = threadIdx.x / 16, uc = threadIdx.x % 16;
+  for (int j0 = 0; j0 < gamma; j0 += kUpdDepth) {
+    float4 ev[2];
+    f4u uv[2];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int n = n0 + ty * 4 + r;
-      acc[r][c] = n < N ? T[(size_t)n * h + f0 + tx * 4 + c] : 0.0f;
+    for (int q = 0; q < 2; ++q) {
+      ev[q] = n0 + er < N ? *(const float4*)(E + (size_t)(n0 + er) * gamma + j0 + 4 * ej + 16 * q)
+                          : float4{0.f, 0.f, 0.f, 0.f};
+      uv[q] = *(const f4u*)(U + (size_t)(b0 + j0 + uj + 16 * q) * h + f0 + 4 * uc);
     }
-  for (int j = 0; j < gamma; ++j) {
-    float ev[4], uv[4];
+    __syncthreads();  // the previous depth step has been read
 #pragma unroll
-    for (int r = 0; r < 4; ++r) ev[r] = es[(ty * 4 + r) * (gamma + 1) + j];
+    for (int q = 0; q < 2; ++q) {
+      const int j = 4 * ej + 16 * q;
+      es[j][er] = ev[q].x; es[j + 1][er] = ev[q].y; es[j + 2][er] = ev[q].z; es[j + 3][er] = ev[q].w;
+      *(float4*)&us[uj + 16 * q][4 * uc] = float4{uv[q].x, uv[q].y, uv[q].z, uv[q].w};
+    }
+    __syncthreads();
+#pragma unroll 8
+    for (int j = 0; j < kUpdDepth; ++j) {
+      const float4 a = *(const float4*)&es[j][4 * ty], b = *(const float4*)&us[j][4 * tx];
+      const float ea[4] = {a.x, a.y, a.z, a.w}, ub[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
-    for (int c = 0; c < 4; ++c) uv[c] = us[j * kUpdCols + tx * 4 + c];
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(-ev[r], uv[c], acc[r][c]);
+        for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(-ea[r], ub[c], acc[r][c]);
+    }
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int n = n0 + ty * 4 + r;
     if (n < N)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) T[(size_t)n * h + f0 + tx * 4 + c] = acc[r][c];
+      *(float4*)(T + (size_t)n * h + f0 + tx * 4) =
+          float4{acc[r][0], acc[r][1], acc[r][2], acc[r][3]};
   }
 }
 
@@ -437,14 +560,15 @@ hipError_t launch_calib_factor(const float* X, int tokens, int n, double lambda,
   info_init_kernel<<<1, 1, 0, s>>>(info);
   hessian_kernel<<<dim3(nb, nb), 256, 0, s>>>(X, tokens, n, lambda, A);
   for (int k = 0; k < nb; ++k) {
-    potrf_diag_kernel<<<1, 256, 0, s>>>(A, n, k, info);
+    potrf_diag_kernel<<<1, 64, 0, s>>>(A, n, k, info);
     if (k + 1 < nb) {
       trsm_kernel<<<nb - k - 1, 64, 0, s>>>(A, n, k);
       chol_update_kernel<<<dim3(nb - k - 1, nb - k - 1), 256, 0, s>>>(A, n, k);
     }
   }
   trinv_diag_kernel<<<nb, 64, 0, s>>>(A, M, n);
-  for (int i = 1; i < nb; ++i) trinv_row_kernel<<<i, 256, 0, s>>>(A, M, n, i);
+  for (int m = 0; m + 1 < nb; ++m)
+    trinv_step_kernel<<<dim3(m + 1, nb - m - 1), 256, 0, s>>>(A, M, n, m);
   const size_t total = (size_t)n * n;
   reverse_round_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(M, U, n);
   return hipGetLastError();
@@ -463,21 +587,20 @@ hipError_t launch_pack_calibrated(const float* W, const float* U, int gamma,
   float* E = R + (size_t)N * h;
   const size_t count = (size_t)N * h;
   const unsigned cgrid = (unsigned)((count + 255) / 256);
-  const int rgrid = (N + 63) / 64;
+  const int rgrid = (N + kQuantRows * kQuantWaves - 1) / (kQuantRows * kQuantWaves);
   for (int e = 0; e < m.E; ++e) {
     const float* We = W + (size_t)e * count;
     for (int lev = 0; lev < m.levels(); ++lev) {
       copy_rows_kernel<<<cgrid, 256, 0, s>>>(lev == 0 ? We : R, T, count);
       for (int b0 = 0; b0 < h; b0 += gamma) {
-        if (m.group == 64)
-          calib_quant_kernel<64><<<rgrid, 64, 0, s>>>(We, T, R, U, E, m, out->planes,
-                                                      out->scales, out->zeros, e, lev, b0, gamma);
-        else
-          calib_quant_kernel<128><<<rgrid, 64, 0, s>>>(We, T, R, U, E, m, out->planes,
-                                                       out->scales, out->zeros, e, lev, b0, gamma);
+        auto quant = m.group == 128 ? calib_quant_kernel<128, 128>
+                     : gamma == 128 ? calib_quant_kernel<64, 128>
+                                    : calib_quant_kernel<64, 64>;
+        quant<<<rgrid, 64 * kQuantWaves, 0, s>>>(We, T, R, U, E, m, out->planes, out->scales,
+                                                 out->zeros, e, lev, b0);
         if (b0 + gamma < h)
-          calib_update_kernel<<<dim3((h - b0 - gamma) / kUpdCols, rgrid), 128, 0, s>>>(
-              T, U, E, N, h, b0, gamma);
+          calib_update_kernel<<<dim3((h - b0 - gamma) / kUpdTile, (N + kUpdTile - 1) / kUpdTile),
+                                256, 0, s>>>(T, U, E, N, h, b0, gamma);
       }
     }
   }
