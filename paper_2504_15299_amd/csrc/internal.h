@@ -81,9 +81,9 @@ struct FwdWorkspace {
   size_t sched_off, h_off, hs_off, y_off, ys_off, xb_off;
   size_t elist_off, xq13_off, xs13_off, h32_off, xq2_off, xs2_off, hmax_off;
   size_t total;
-  int chunk_n, schunk_n;  // grouped-GEMM chunk-table entries (routed, shared)
-  int shared_chunk;       // positions per chunk of the shared expert
-  int shared_ksplit;      // parts of the shared W2 reduction (partial sums summed by combine)
+  int chunk_n;        // 16-byte units of the routed chunk table (the shared one follows)
+  int shared_chunk;   // positions per chunk of the shared expert in the tile GEMM
+  int shared_ksplit;  // parts of the shared W2 reduction (partial sums summed by combine)
 };
 
 struct DecodeBuffers {
@@ -99,6 +99,20 @@ bool decode_path_ok(const d2moe_mwq* w13, const d2moe_mwq* w2, int T);
 hipError_t launch_decode_ffn(const void* x, d2moe_dtype xd, int T, int d, int d_ff, int E, int k,
                              const d2moe_mwq* w13, const d2moe_mwq* w2, const d2moe_routing* r,
                              const DecodeBuffers& b, hipStream_t s, const hipEvent_t* events);
+// The LDS-tile grouped GEMM (ffn_tile.hip): h = silu(W1 x) * (W3 x) and y = W2 h
+// over *count chunks (device, at most n_ub) of four words each, first
+// position, positions, bit-width, expert: chunk c at `last` - 4 c.
+constexpr int kTileChunk = 256;  // positions per chunk
+hipError_t launch_tile_gemm13(const uint16_t* x, const int32_t* perm, int k, const d2moe_mwq* w13,
+                              const int32_t* count, const int32_t* last, int n_ub, uint16_t* h,
+                              hipStream_t s);
+hipError_t launch_tile_gemm2(const uint16_t* h, const d2moe_mwq* w2, const int32_t* count,
+                             const int32_t* last, int n_ub, float* y, hipStream_t s);
+// The shared expert on it: T positions in chunks of cs, the W2 reduction in
+// ksplit parts of T rows each in y; chunks: table of (T + cs - 1) / cs entries.
+hipError_t launch_tile_shared(const uint16_t* x, int T, const d2moe_mwq* w13, const d2moe_mwq* w2,
+                              int bits, int cs, int ksplit, int32_t* chunks, uint16_t* h, float* y,
+                              hipStream_t s);
 FwdWorkspace fwd_workspace_layout(int T, int d, int d_ff, int E, int k, int shared_d_ff);
 
 hipError_t launch_forward_streamed(const void* x, d2moe_dtype xd, int T, int d, int d_ff, int E,
@@ -123,9 +137,8 @@ hipError_t launch_stream_read(const void* buf, size_t bytes, uint32_t* sink, int
 hipError_t launch_residual_rmsnorm(float* x, const void* y, d2moe_dtype yd, int T, int d,
                                    float eps, void* h, d2moe_dtype hd, hipStream_t s);
 
-// concurrent: independent parts of the layer (the shared expert, the
-// narrow routed chunks) may run on this host thread's side streams of the
-// current device, forked from and joined back to `s` with events.
+// concurrent: the shared expert may run on this host thread's side stream of
+// the current device, forked from and joined back to `s` with events.
 hipError_t launch_forward(const void* x, d2moe_dtype xd, int T, int d, int d_ff, int E, int k,
                           const d2moe_mwq* w13, const d2moe_mwq* w2, const d2moe_routing* r,
                           const d2moe_mwq* sw13, const d2moe_mwq* sw2, int shared_bits,
