@@ -114,3 +114,52 @@ def test_streamed_forward_partly_resident():
                                    [torch.cuda.Event() for _ in units], io)
     torch.cuda.synchronize()
     assert np.array_equal(got.float().cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("host", ["pinned_interior", "pageable"])
+@pytest.mark.parametrize("group", [64, 128])
+def test_streamed_copy_paths(host, group):
+    """Pinned weights that start inside a larger allocation are read by the
+    device; ordinary host memory takes the runtime's strided copies.  Either
+    way the device copy ends with exactly the planes, scales and zero points
+    that the units load, and the output is the resident forward's."""
+    s = wl.scaled(wl.mixtral_decode(T=80), d=256, f=256, group=group)
+    L = Layer(s).pack()
+    r = L.route()
+    torch.cuda.synchronize()
+    want = L.forward()
+    hist = r.hist.cpu().numpy()
+
+    def to_host(t):
+        if host == "pageable":
+            return t.cpu()
+        buf = torch.empty(t.numel() * t.element_size() + 4096, dtype=torch.uint8, pin_memory=True)
+        view = buf[4096:].view(t.dtype)
+        view.copy_(t)
+        return view
+
+    def host_mwq(m):
+        return api.MWQ(m.n_experts, m.rows, m.cols, m.group, m.b_min, m.b_max, to_host(m.planes),
+                       to_host(m.scales), to_host(m.zeros))
+
+    h13, h2 = host_mwq(L.w13), host_mwq(L.w2)
+    d13, d2 = _empty_like(L.w13), _empty_like(L.w2)
+    resident = np.zeros(s.E, np.uint8)
+    units = api.hebf_order(hist, s.b_min, s.b_max)
+    got = api.moe_forward_streamed(L.xt, h13, h2, d13, d2, resident, r, s.k, hist, units,
+                                   [torch.cuda.Event() for _ in units], torch.cuda.Stream())
+    torch.cuda.synchronize()
+    assert np.array_equal(got.float().cpu().numpy(), want)
+    for m, d in ((L.w13, d13), (L.w2, d2)):
+        top = {e: int(resident[e]) for e in range(s.E)}
+        nblk = m.rows * m.group // 2048 * (m.cols // m.group)
+        planes = m.planes.view(s.E, nblk, m.b_max, 64), d.planes.view(s.E, nblk, m.b_max, 64)
+        lev = m.b_max - m.b_min + 1
+        scales = m.scales.view(s.E, nblk, lev, -1), d.scales.view(s.E, nblk, lev, -1)
+        zeros = m.zeros.view(s.E, -1), d.zeros.view(s.E, -1)
+        for e, b in top.items():
+            if b:
+                assert torch.equal(planes[0][e, :, :b], planes[1][e, :, :b])
+                assert torch.equal(scales[0][e, :, :b - m.b_min + 1],
+                                   scales[1][e, :, :b - m.b_min + 1])
+                assert torch.equal(zeros[0][e], zeros[1][e])
