@@ -1364,10 +1364,15 @@ hipError_t launch_decode_ffn(const void* x, d2moe_dtype xd, int T, int d, int d_
   // adjacent row blocks over a quarter of the reduction (decode13_kernel, one
   // activation load for both blocks); with fewer work items (batches below
   // 8 at the Mixtral shape) the 4-wave-per-row-block kernel keeps more
-  // streams in flight and is faster.  The second block's offset is one row
-  // block of groups.
+  // streams in flight and is faster.  With two or three column blocks, whose
+  // activation loads weigh more and whose waves are fewer per SIMD, pairs win
+  // from a quarter of that: one dense expert, d 5120, d_ff 13824, took 77, 94
+  // and 171 us per layer at 16, 24 and 64 tokens against 85, 106 and 195; at d
+  // 2048, 512 waves, they lose, 52 against 46.  The second block's offset is
+  // one row block of groups.
   constexpr int kW2Split = 4;
-  const bool pairs2 = (d / 16) % 2 == 0 && (long)(d / 32) * ny * kW2Split >= 5120;
+  const bool pairs2 =
+      (d / 16) % 2 == 0 && (long)(d / 32) * ny * kW2Split >= (ncb == 1 ? 5120 : 1280);
   if (pairs2 && ncb == 1)
     err = launch_decode13_kernel<kW2Split, 1, false>(w2->b_min, ny, W2, b.elist, b.xq2, b.xs2,
                                                      npos, d, b.y, d, nullptr, s, e2, e3);
