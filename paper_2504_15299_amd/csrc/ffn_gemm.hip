@@ -83,6 +83,7 @@ struct GemmWork {
 // Longest workgroups first: experts (buckets) of the largest bit-width, then of
 // the most positions.  One workgroup of kChunkThreads threads, one per expert
 // (E <= 64) and one per bucket (E L <= 512).
+__host__ __device__ inline bool on_tiles(int tiles, int reg) { return 17 * tiles < 10 * reg; }
 constexpr int kChunkThreads = 512;
 constexpr int kTileAverage = 384;
 __global__ __launch_bounds__(kChunkThreads) void chunk_kernel(
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_kernel(
       if (n > 0) mb = l + 1;
     }
     const int reg = (tot + kBlocks - 1) / kBlocks;
-    const bool tile = all_tile || 17 * tiles < 10 * reg;
+    const bool tile = all_tile || on_tiles(tiles, reg);
     on_tile[j] = tile;
     rkey[j] = (mb << 24) + min(tot, (1 << 24) - 1);
     nreg[j] = tile ? 0 : reg;
@@ -216,12 +217,15 @@ struct RawTile {
 //           reduction in plane blockIdx.y (out_split values apart)
 // BMIN > 0 fixes b_min at compile time (the common ladder starts at 2 bits);
 // BMIN == 0 takes it from W.
-template <int G, bool SWIGLU, int BMIN>
-__global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(2)))
+// KS = 2 (the plain variant only): two such groups of four waves per workgroup,
+// each with its own stages, take the first and the second half of the
+// reduction, and the first adds the second's sums at the end.
+template <int G, bool SWIGLU, int BMIN, int KS>
+__global__ __launch_bounds__(KS * kGemmThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void bgemm_kernel(const uint16_t* __restrict__ in, int in_ld, const int32_t* __restrict__ perm,
                   int kdiv, MwqView W, GemmWork wk, int tiles, int f, int N,
                   void* __restrict__ out, int out_ld, size_t out_split) {
-  __shared__ __attribute__((aligned(1024))) uint8_t xs[2][kStageBytes];
+  __shared__ __attribute__((aligned(1024))) uint8_t xs_all[KS][2][kStageBytes];
   // first 16-byte unit of each position's activation row (kept in LDS rather
   // than in registers, and read before a step's DMA)
   __shared__ __attribute__((aligned(16))) uint32_t xrow_at[kBlockPos][kBlocks];
@@ -231,7 +235,9 @@ void bgemm_kernel(const uint16_t* __restrict__ in, int in_ld, const int32_t* __r
 
   const int chunk = blockIdx.x / tiles, tile = blockIdx.x % tiles;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = wave_all & (kGemmWaves - 1), kg = KS > 1 ? wave_all / kGemmWaves : 0;
+  uint8_t (&xs)[2][kStageBytes] = xs_all[kg];
   const int r = lane & 15, q = lane >> 4;
   const int b_min = BMIN > 0 ? BMIN : W.b_min;
 
@@ -299,8 +305,16 @@ void bgemm_kernel(const uint16_t* __restrict__ in, int in_ld, const int32_t* __r
   }
   __syncthreads();
   const int nall = (K + kStepK - 1) / kStepK;
-  const int it0 = SWIGLU ? 0 : (int)((long)blockIdx.y * nall / gridDim.y);
-  const int it1 = SWIGLU ? nall : (int)((long)(blockIdx.y + 1) * nall / gridDim.y);
+  // this group's steps; both groups run `steps` of them (the second one's last
+  // may be past its end: it only keeps the barriers in step)
+  const int part = blockIdx.y * KS + kg, parts = gridDim.y * KS;
+  const int it0 = SWIGLU ? 0 : (int)((long)part * nall / parts);
+  const int it1 = SWIGLU ? nall : (int)((long)(part + 1) * nall / parts);
+  int steps = it1 - it0;
+  if (KS > 1) {
+    const int o = blockIdx.y * KS + (kg ^ 1);
+    steps = max(steps, (int)((long)(o + 1) * nall / parts) - (int)((long)o * nall / parts));
+  }
   auto x_dma = [&](int it) {
     uint8_t* dst = xs[it & 1] + 1024 * wave;
     uint32_t xoff[kBlocks];
@@ -385,8 +399,9 @@ void bgemm_kernel(const uint16_t* __restrict__ in, int in_ld, const int32_t* __r
   for (int s = 0; s < 4; ++s)
     xaddr[s] = lds_addr(xs[0]) + 256 * r + 16 * slot_of_chunk(q, s, r);
 
-  x_dma(it0);
-  at_step(it0);
+  // a group without steps still loads one (unused, within the matrix)
+  x_dma(min(it0, nall - 1));
+  at_step(min(it0, nall - 1));
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     raw[t] = RawTile{};
@@ -397,12 +412,13 @@ void bgemm_kernel(const uint16_t* __restrict__ in, int in_ld, const int32_t* __r
         if (p < bits) load_plane(t, p);
     }
   }
-  for (int it = it0; it < it1; ++it) {
+  for (int it = it0; it < it0 + steps; ++it) {
     // everything issued in the previous step has landed: this step's
     // activations (every wave's, after the barrier) and raw words.  The
     // barrier also ends every read of the stage that is filled next.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
+    if (KS > 1 && it >= it1) continue;
     if (!active) {
       if (it + 1 < it1) x_dma(it + 1);
       continue;
@@ -518,6 +534,23 @@ void bgemm_kernel(const uint16_t* __restrict__ in, int in_ld, const int32_t* __r
     });
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if constexpr (KS > 1) {
+    // the second group's sums through its own stages, which no one reads now
+    __syncthreads();
+    f32x4* sums = (f32x4*)xs_all[KS - 1] + (size_t)wave * (2 * kBlocks * 64) + lane;
+    static_assert(kGemmWaves * 2 * kBlocks * 64 * 16 <= 2 * kStageBytes, "the sums fit");
+    if (kg != 0)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < kBlocks; ++i) sums[64 * (kBlocks * t + i)] = acc[t][i];
+    __syncthreads();
+    if (kg != 0) return;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < kBlocks; ++i) acc[t][i] += sums[64 * (kBlocks * t + i)];
+  }
   if (!active) return;
 
   // ---- epilogue: lane (r, q) holds position r of every block, rows 4 q ..
@@ -728,6 +761,12 @@ int tile_bound(int n, int L, int E) {
   return (int)((n / kBlockPos + L * experts) / kBlocks);
 }
 
+// About how many register chunks there will be: one per active expert and one
+// more per 256 positions.
+int chunk_estimate(int T, int k, int E) {
+  return (E < T * k ? E : T * k) + T * k / (2 * kBlocks * kBlockPos);
+}
+
 // Slots of four words of the chunk table: one per bucket and one per 256
 // positions.  An expert's register chunks are no more than its tile chunks
 // wherever it takes the former, so both tables together have at most
@@ -767,28 +806,41 @@ void shared_plan(int T, int d, int shared_d_ff, int* cs, int* ksplit) {
 template <int G, bool SWIGLU>
 hipError_t run_gemm_g(const uint16_t* in, int in_ld, const int32_t* perm, int kdiv,
                       const MwqView& W, const GemmWork& wk, int n_ub, void* out, int out_ld,
-                      hipStream_t s, int ksplit, size_t out_split) {
+                      hipStream_t s, int ksplit, size_t out_split, int n_chunks) {
   const int N = SWIGLU ? W.rows / 2 : W.rows;
   const int per = SWIGLU ? kTileRows / 2 : kTileRows;
   const int tiles = (N + per - 1) / per;
   const dim3 grid((unsigned)((long)n_ub * tiles), ksplit);
+  const long n_wg = (long)n_chunks * tiles * ksplit;
+  // W2 in two groups where its workgroups would fill less than about two thirds
+  // of the GPU's 512 places for them (n_wg: about as many as there will be) and
+  // each group still has a few steps.  Mixtral shape, ms per step in one group /
+  // two: 70 tokens (256 workgroups of 112 steps) 0.99 / 0.93, 301 (320) 1.14 /
+  // 1.06, 512 (384) 1.31 / 1.35.
+  const bool two = !SWIGLU && n_wg <= 352 && W.cols / kStepK / ksplit >= 8;
+  auto launch = [&](auto kernel, int threads) {
+    kernel<<<grid, threads, 0, s>>>(in, in_ld, perm, kdiv, W, wk, tiles, N, N, out, out_ld,
+                                    out_split);
+  };
+  constexpr int KS2 = SWIGLU ? 1 : 2;
   if (W.b_min == 2)
-    bgemm_kernel<G, SWIGLU, 2><<<grid, kGemmThreads, 0, s>>>(in, in_ld, perm, kdiv, W, wk, tiles, N,
-                                                            N, out, out_ld, out_split);
+    two ? launch(bgemm_kernel<G, SWIGLU, 2, KS2>, KS2 * kGemmThreads)
+        : launch(bgemm_kernel<G, SWIGLU, 2, 1>, kGemmThreads);
   else
-    bgemm_kernel<G, SWIGLU, 0><<<grid, kGemmThreads, 0, s>>>(in, in_ld, perm, kdiv, W, wk, tiles, N,
-                                                            N, out, out_ld, out_split);
+    two ? launch(bgemm_kernel<G, SWIGLU, 0, KS2>, KS2 * kGemmThreads)
+        : launch(bgemm_kernel<G, SWIGLU, 0, 1>, kGemmThreads);
   return hipGetLastError();
 }
+// n_ub bounds the chunks of `wk`, n_chunks is about how many there will be.
 template <bool SWIGLU>
 hipError_t run_gemm(const uint16_t* in, int in_ld, const int32_t* perm, int kdiv, const MwqView& W,
-                    const GemmWork& wk, int n_ub, void* out, int out_ld, hipStream_t s,
-                    int ksplit = 1, size_t out_split = 0) {
+                    const GemmWork& wk, int n_ub, int n_chunks, void* out, int out_ld,
+                    hipStream_t s, int ksplit = 1, size_t out_split = 0) {
   if (n_ub <= 0) return hipSuccess;
   return W.group == 128 ? run_gemm_g<128, SWIGLU>(in, in_ld, perm, kdiv, W, wk, n_ub, out, out_ld,
-                                                  s, ksplit, out_split)
+                                                  s, ksplit, out_split, n_chunks)
                         : run_gemm_g<64, SWIGLU>(in, in_ld, perm, kdiv, W, wk, n_ub, out, out_ld,
-                                                 s, ksplit, out_split);
+                                                 s, ksplit, out_split, n_chunks);
 }
 
 // The work of one bucket: `cnt` positions from `first` at `bits` bits of
@@ -872,7 +924,7 @@ hipError_t side_stream(SideStream** out) {
 // the copy of the next unit overlaps the computation of this one.  The
 // per-position arithmetic is that of the grouped GEMM path of
 // launch_forward (how positions are grouped into blocks and chunks does not
-// change a position's sums).
+// change a position's sums; which GEMM an expert takes does).
 hipError_t launch_forward_streamed(const void* x, d2moe_dtype xd, int T, int d, int d_ff, int E,
                                    int k, const d2moe_mwq* hw13, const d2moe_mwq* hw2,
                                    const d2moe_mwq* w13, const d2moe_mwq* w2, uint8_t* resident,
@@ -898,6 +950,21 @@ hipError_t launch_forward_streamed(const void* x, d2moe_dtype xd, int T, int d, 
   off[0] = 0;
   for (int i = 0; i < E * Lv; ++i) off[i + 1] = off[i] + hist_host[i];
   const MwqView W13 = view_of(w13), W2 = view_of(w2);
+  // the same GEMM for an expert, and the same split of W2, as in
+  // launch_forward, so that a position's sums are the same bit for bit
+  int32_t* table = (int32_t*)(base + L.sched_off);
+  const bool all_tile = (long)T * k >= (long)kTileAverage * E;
+  const int n_chunks = chunk_estimate(T, k, E);
+  bool tile[64];
+  for (int e = 0; e < E; ++e) {
+    int blocks = 0, tiles = 0;
+    for (int l = 0; l < Lv; ++l) {
+      const int n = hist_host[e * Lv + l];
+      blocks += (n + kBlockPos - 1) / kBlockPos;
+      tiles += (n + kTileChunk - 1) / kTileChunk;
+    }
+    tile[e] = all_tile || on_tiles(tiles, (blocks + kBlocks - 1) / kBlocks);
+  }
   const uint8_t *host13[3], *host2[3];
   const bool by_kernel = delta_addresses(hw13, w13, host13) && delta_addresses(hw2, w2, host2);
   for (int i = 0; i < n_units; ++i) {
@@ -917,11 +984,18 @@ hipError_t launch_forward_streamed(const void* x, d2moe_dtype xd, int T, int d, 
     if ((err = hipStreamWaitEvent(s, events[i], 0)) != hipSuccess) return err;
     if (resident[u.expert] < u.load_to) resident[u.expert] = (uint8_t)u.load_to;
     if (u.count <= 0) continue;
+    const int first = off[u.expert * Lv + (u.bits - b_min)];
+    if (tile[u.expert]) {
+      err = launch_tile_bucket(xb, r->perm, k, w13, w2, first, u.count, u.bits, u.expert, table, h,
+                               y, s);
+      if (err != hipSuccess) return err;
+      continue;
+    }
     int n_ub;
-    const GemmWork wk = one_bucket(off[u.expert * Lv + (u.bits - b_min)], u.count, u.bits, u.expert, &n_ub);
-    err = run_gemm<true>(xb, d, r->perm, k, W13, wk, n_ub, h, d_ff, s);
+    const GemmWork wk = one_bucket(first, u.count, u.bits, u.expert, &n_ub);
+    err = run_gemm<true>(xb, d, r->perm, k, W13, wk, n_ub, n_chunks, h, d_ff, s);
     if (err != hipSuccess) return err;
-    err = run_gemm<false>(h, d_ff, nullptr, 1, W2, wk, n_ub, y, d, s);
+    err = run_gemm<false>(h, d_ff, nullptr, 1, W2, wk, n_ub, n_chunks, y, d, s);
     if (err != hipSuccess) return err;
   }
   if (T == 0) return hipSuccess;
@@ -985,9 +1059,9 @@ hipError_t launch_forward(const void* x, d2moe_dtype xd, int T, int d, int d_ff,
     } else {
       int ns_ub;
       const GemmWork wk = one_bucket(0, T, shared_bits, 0, &ns_ub);
-      err = run_gemm<true>(xb, d, nullptr, 1, view_of(sw13), wk, ns_ub, hs, shared_d_ff, ss);
+      err = run_gemm<true>(xb, d, nullptr, 1, view_of(sw13), wk, ns_ub, ns_ub, hs, shared_d_ff, ss);
       if (err != hipSuccess) return err;
-      err = run_gemm<false>(hs, shared_d_ff, nullptr, 1, view_of(sw2), wk, ns_ub, ys, d, ss,
+      err = run_gemm<false>(hs, shared_d_ff, nullptr, 1, view_of(sw2), wk, ns_ub, ns_ub, ys, d, ss,
                             L.shared_ksplit, (size_t)T * d);
       if (err != hipSuccess) return err;
     }
@@ -1012,19 +1086,22 @@ hipError_t launch_forward(const void* x, d2moe_dtype xd, int T, int d, int d_ff,
                                             all_tile, table);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     const int n_ub = all_tile ? 0 : chunk_bound(T * k, Lv, E);
-    const int nt_ub = all_tile ? L.chunk_n - 1 : tile_bound(T * k, Lv, E);
+    // an expert holds at most T positions, one per token
+    const int nt_ub =
+        all_tile ? L.chunk_n - 1 : T > kBlocks * kBlockPos ? tile_bound(T * k, Lv, E) : 0;
+    const int n_chunks = chunk_estimate(T, k, E);
     const GemmWork wk{table, r->hist, r->offsets, Lv, 0, 0, 0, 0, 0};
     const int32_t* tiles = table + 4 * (size_t)(L.chunk_n - 1);
     if (events && (err = hipEventRecord(events[0], s)) != hipSuccess) return err;
     err = launch_tile_gemm13(xb, r->perm, k, w13, table + 1, tiles, nt_ub, h, s);
     if (err != hipSuccess) return err;
-    err = run_gemm<true>(xb, d, r->perm, k, view_of(w13), wk, n_ub, h, d_ff, s);
+    err = run_gemm<true>(xb, d, r->perm, k, view_of(w13), wk, n_ub, n_chunks, h, d_ff, s);
     if (err != hipSuccess) return err;
     if (events && (err = hipEventRecord(events[1], s)) != hipSuccess) return err;
     if (events && (err = hipEventRecord(events[2], s)) != hipSuccess) return err;
     err = launch_tile_gemm2(h, w2, table + 1, tiles, nt_ub, y, s);
     if (err != hipSuccess) return err;
-    err = run_gemm<false>(h, d_ff, nullptr, 1, view_of(w2), wk, n_ub, y, d, s);
+    err = run_gemm<false>(h, d_ff, nullptr, 1, view_of(w2), wk, n_ub, n_chunks, y, d, s);
     if (err != hipSuccess) return err;
     if (events && (err = hipEventRecord(events[3], s)) != hipSuccess) return err;
   }

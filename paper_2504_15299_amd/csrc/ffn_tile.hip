@@ -529,14 +529,15 @@ __attribute__((amdgpu_waves_per_eu(2))) void tile_gemm_kernel(
   }
 }
 
-// Chunk table of one bucket: cnt positions from 0 at `bits` bits of expert 0, in
-// chunks of cs.
-__global__ void tile_bucket_kernel(int cnt, int bits, int cs, int n, int32_t* __restrict__ chunks) {
+// Chunk table of one bucket: cnt positions from `first` at `bits` bits of
+// `expert`, in chunks of cs.
+__global__ void tile_bucket_kernel(int first, int cnt, int bits, int expert, int cs, int n,
+                                   int32_t* __restrict__ chunks) {
   for (int c = threadIdx.x; c < n; c += blockDim.x) {
-    chunks[4 * c] = c * cs;
+    chunks[4 * c] = first + c * cs;
     chunks[4 * c + 1] = min(cs, cnt - c * cs);
     chunks[4 * c + 2] = bits;
-    chunks[4 * c + 3] = 0;
+    chunks[4 * c + 3] = expert;
   }
 }
 
@@ -565,13 +566,25 @@ hipError_t launch_tile_shared(const uint16_t* x, int T, const d2moe_mwq* w13, co
                               int bits, int cs, int ksplit, int32_t* chunks, uint16_t* h, float* y,
                               hipStream_t s) {
   const int n = (T + cs - 1) / cs, f = w13->rows / 2, d = w2->rows;
-  tile_bucket_kernel<<<1, 256, 0, s>>>(T, bits, cs, n, chunks);
+  tile_bucket_kernel<<<1, 256, 0, s>>>(0, T, bits, 0, cs, n, chunks);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   err = run_tile_gemm<true>(x, w13->cols, nullptr, 1, view_of(w13), nullptr, chunks, 4, n, f, h, f, s);
   if (err != hipSuccess) return err;
   return run_tile_gemm<false>(h, f, nullptr, 1, view_of(w2), nullptr, chunks, 4, n, f, y, d, s,
                               ksplit, (size_t)T * d);
+}
+
+hipError_t launch_tile_bucket(const uint16_t* x, const int32_t* perm, int k, const d2moe_mwq* w13,
+                              const d2moe_mwq* w2, int first, int cnt, int bits, int expert,
+                              int32_t* chunks, uint16_t* h, float* y, hipStream_t s) {
+  const int n = (cnt + kTileChunk - 1) / kTileChunk, f = w13->rows / 2, d = w2->rows;
+  tile_bucket_kernel<<<1, 256, 0, s>>>(first, cnt, bits, expert, kTileChunk, n, chunks);
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  err = run_tile_gemm<true>(x, w13->cols, perm, k, view_of(w13), nullptr, chunks, 4, n, f, h, f, s);
+  if (err != hipSuccess) return err;
+  return run_tile_gemm<false>(h, f, nullptr, 1, view_of(w2), nullptr, chunks, 4, n, f, y, d, s);
 }
 
 hipError_t launch_tile_gemm13(const uint16_t* x, const int32_t* perm, int k, const d2moe_mwq* w13,

@@ -108,6 +108,10 @@ hipError_t launch_tile_gemm13(const uint16_t* x, const int32_t* perm, int k, con
                               hipStream_t s);
 hipError_t launch_tile_gemm2(const uint16_t* h, const d2moe_mwq* w2, const int32_t* count,
                              const int32_t* last, int n_ub, float* y, hipStream_t s);
+// One (expert, bit-width) bucket on it, its chunk table written to `chunks`.
+hipError_t launch_tile_bucket(const uint16_t* x, const int32_t* perm, int k, const d2moe_mwq* w13,
+                              const d2moe_mwq* w2, int first, int cnt, int bits, int expert,
+                              int32_t* chunks, uint16_t* h, float* y, hipStream_t s);
 // The shared expert on it: T positions in chunks of cs, the W2 reduction in
 // ksplit parts of T rows each in y; chunks: table of (T + cs - 1) / cs entries.
 hipError_t launch_tile_shared(const uint16_t* x, int T, const d2moe_mwq* w13, const d2moe_mwq* w2,

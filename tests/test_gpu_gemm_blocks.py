@@ -23,6 +23,7 @@ CASES = {
     "nine_blocks": (5, 8, 64, 320, 64, {5: 33, 6: 17, 7: 16, 8: 33}),
     "chunk_edge_128": (2, 8, 128, 256, 128, {4: 128}),
     "chunk_edge_129": (2, 4, 128, 384, 256, {2: 113, 4: 16}),
+    "ks2_long_reduction": (2, 8, 64, 128, 1088, {2: 20, 8: 3}),
     "two_chunks_mixed": (3, 8, 128, 256, 128, {3: 100, 5: 1, 8: 150}),
     "long_run": (8, 8, 64, 64, 64, {8: 257}),
     # one width of more than 128 positions, and 384 positions per expert and

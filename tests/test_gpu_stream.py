@@ -47,7 +47,7 @@ def _ascending(hist, b_min, resident):
     return units
 
 
-@pytest.mark.parametrize("T", [80, 16])
+@pytest.mark.parametrize("T", [80, 16, 900])
 def test_streamed_forward_matches_resident(T):
     s = wl.scaled(wl.mixtral_decode(T=T), d=512, f=384)
     L = Layer(s).pack()
