@@ -21,7 +21,7 @@
 // so a lane holds a and c of the same output and applies SwiGLU in registers.
 #include <type_traits>
 
-#include "internal.h"
+#include "lookup.h"
 
 namespace d2moe {
 namespace {
@@ -63,12 +63,13 @@ constexpr int kWTile = kTileRows * kStepK * 2;  // dequantized bf16 tile bytes
 
 __device__ inline float silu(float a) { return a / (1.0f + __expf(-a)); }
 
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+using lookup::as_h2;
+using lookup::as_u;
+using lookup::h2;
+using lookup::rotr;
 typedef float f2 __attribute__((ext_vector_type(2)));
 typedef __bf16 b2 __attribute__((ext_vector_type(2)));
 
-__device__ inline h2 as_h2(uint32_t v) { return __builtin_bit_cast(h2, v); }
-__device__ inline uint32_t as_u(h2 v) { return __builtin_bit_cast(uint32_t, v); }
 __device__ inline uint32_t h2_splat(float v) {
   const _Float16 h = (_Float16)v;
   return as_u(h2{h, h});
@@ -103,8 +104,8 @@ __device__ inline void ldu8(uint32_t& v, uint32_t a) {
   static_assert(OFF >= 0 && OFF < 65536, "ds offset");
   asm volatile("ds_read_u8 %0, %1 offset:%2" : "=v"(v) : "v"(a), "n"(OFF) : "memory");
 }
-__device__ inline void st128(uint32_t a, uint32_t x, uint32_t y, uint32_t z, uint32_t w) {
-  asm volatile("ds_write_b128 %0, %1" ::"v"(a), "v"(u32x4{x, y, z, w}) : "memory");
+__device__ inline void st64(uint32_t a, uint32_t x, uint32_t y) {
+  asm volatile("ds_write_b64 %0, %1" ::"v"(a), "v"(u32x2{x, y}) : "memory");
 }
 __device__ inline void wait_lgkm() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 template <int N>
@@ -154,58 +155,84 @@ struct StepRegs {
   }
 };
 
-// Dequantization of four weight pairs (columns j, j + 16 for
-// j = 4 dq .. 4 dq + 3) of a tile row at MB planes into bf16 pairs for the
-// tile (o[0..1] columns 4 dq .. 4 dq + 3, o[2..3] columns 16 + 4 dq ..).
-// It works on pairs in packed fp16: shifting a plane word left by 15 - j puts
-// bit j at bit 15 and bit j + 16 at bit 31, the sign positions of the two
-// halves, and one and-or turns the pair into (+-c_p, +-c_p).  With every plane
-// read as a sign,
+// Dequantization of 16 weights (columns j0 + j, j0 + 8 + j, j0 + 16 + j and
+// j0 + 24 + j for j < 4) of a tile row at MB planes into bf16 pairs: o[2 c],
+// o[2 c + 1] columns 8 c + j0 .. + 3.
+// With every plane read as a sign,
 //   W^_b = s1 (Q - z) + sum_{p>=b_min} s_p sigma_p
 //        = C + sum_{p<b} c_p (2 bit_p - 1),  c_p = s1 2^(p-1) for p < b_min,
 //          c_p = s_p for p >= b_min,  C = s1 ((2^b_min - 1) / 2 - z),
-// accumulated in fp16 from C, then rounded to bf16 for the MFMA.  Every scale
-// is >= 0, so the sign bits of c_p are clear and the and-or only has to set
-// them from the plane bits.  Rows past the matrix edge are dequantized from
-// whatever their stage holds: they only reach output columns that are not
-// stored.
+// accumulated in fp16 from C, then rounded to bf16 for the MFMA.  Planes come
+// by threes and twos by lookup, a plane left over by its sign: shifting its
+// word left by 15 - j puts bit j at bit 15 and bit j + 16 at bit 31, the sign
+// positions of the two halves, and one and-or turns the pair into (+-c_p, +-c_p)
+// (every scale is >= 0, so the sign bits of c_p are clear).
+// Rows past the matrix edge are dequantized from whatever their stage holds:
+// they only reach output columns that are not stored.
+// At 8 bits the vector ALU, not the matrix pipe, bounds a step: 32 products are
+// 512 cycles and the sign form of every plane was about 240 instructions of 4.
+// With lookups about 185; ms per step, Mixtral shape, 2048 tokens: {2,4,8} bits
+// 2.85 -> 2.67, {5,6,7,8} 3.88 -> 3.44; 64 experts top-6, 4096 tokens 1.36 -> 1.28.
 // BMIN > 0 fixes b_min at compile time (the common ladder starts at 2 bits);
 // BMIN == 0 takes it from `b_min_rt`.
 template <int MB, int BMIN>
-__device__ __attribute__((always_inline)) inline void dequant_pairs(
-    const StepRegs& R, int b_min_rt, uint32_t sh_m, int dq, uint32_t (&o)[4]) {
+__device__ __attribute__((always_inline)) inline void dequant16(const StepRegs& R, int b_min_rt,
+                                                                uint32_t sh_m, int j0,
+                                                                uint32_t (&o)[8]) {
   const int b_min = BMIN > 0 ? BMIN : b_min_rt;
   const float s1 = h2f((uint16_t)R.s1);
-  const uint32_t C = h2_splat(s1 * ((float)((1 << b_min) - 1) * 0.5f - (float)R.z));
+  const h2 C = as_h2(h2_splat(s1 * ((float)((1 << b_min) - 1) * 0.5f - (float)R.z)));
   // base scale as a binary16 pair; the pair of a residual plane is its scale
   // bits duplicated, and that of a base plane p < b_min is s1 2^(p-1), a
   // power-of-two multiple in binary16
   const h2 s1p = as_h2(R.s1 | (R.s1 << 16));
-  h2 a[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) a[j] = as_h2(C);
-#pragma unroll
-  for (int p = 0; p < MB; ++p) {
+  auto cp = [&](int p) {
     const _Float16 k = (_Float16)((float)(1 << p) * 0.5f);
-    const uint32_t cp = p < b_min ? as_u(s1p * h2{k, k}) : (R.sp[p] | (R.sp[p] << 16));
+    return p < b_min ? as_u(s1p * h2{k, k}) : (R.sp[p] | (R.sp[p] << 16));
+  };
+  auto w = [&](int p, int n) { return rotr(R.w[p], j0 + 32 - n); };
+  h2 a[8];
+  auto sign = [&](int p) {
+    const uint32_t c = cp(p), wp = rotr(R.w[p], j0);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const uint32_t t = R.w[p] << (15 - (4 * dq + j));
-      const uint32_t v = (sh_m & t) | cp;  // bit set -> -c_p
-      a[j] = a[j] - as_h2(v);
+      a[j] = a[j] - as_h2((sh_m & (wp << (15 - j))) | c);  // bit set -> -c_p
+      a[4 + j] = a[4 + j] - as_h2((sh_m & (wp << (7 - j))) | c);
     }
-  }
-  // (column j, column j + 16) fp16 pairs to bf16 pairs of adjacent columns
-  f2 f[4];
+  };
+  if constexpr (MB == 1) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) f[j] = __builtin_convertvector(a[j], f2);
+    for (int j = 0; j < 8; ++j) a[j] = C;
+    sign(0);
+  } else if constexpr (MB == 2) {
+    lookup::planes2<true, 4>(a, w(0, 0), w(1, 1), cp(0), cp(1), C);
+  } else {
+    lookup::planes3<true, 4>(a, w(0, 0), w(1, 1), w(2, 2), cp(0), cp(1), cp(2), C);
+    if constexpr (MB >= 6)
+      lookup::planes3<false, 4>(a, w(3, 0), w(4, 1), w(5, 2), cp(3), cp(4), cp(5), C);
+    constexpr int P = MB >= 6 ? 6 : 3;
+    if constexpr (MB == P + 2) lookup::planes2<false, 4>(a, w(P, 0), w(P + 1, 1), cp(P), cp(P + 1), C);
+    if constexpr (MB == P + 1) sign(P);
+  }
+  // pairs of columns 16 apart to bf16 pairs of adjacent columns
+  f2 f[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) f[j] = __builtin_convertvector(a[j], f2);
   auto pk = [](float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{lo, hi}, b2));
   };
-  o[0] = pk(f[0].x, f[1].x);  // columns 4 dq, 4 dq + 1
-  o[1] = pk(f[2].x, f[3].x);  // 4 dq + 2, 4 dq + 3
-  o[2] = pk(f[0].y, f[1].y);  // 16 + 4 dq, ...
-  o[3] = pk(f[2].y, f[3].y);
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    o[2 * c] = pk(f[4 * c].x, f[4 * c + 1].x);
+    o[2 * c + 1] = pk(f[4 * c + 2].x, f[4 * c + 3].x);
+    o[4 + 2 * c] = pk(f[4 * c].y, f[4 * c + 1].y);
+    o[4 + 2 * c + 1] = pk(f[4 * c + 2].y, f[4 * c + 3].y);
+  }
+}
+// Vector instructions of dequant16, about.
+constexpr int dequant_ops(int mb) {
+  constexpr int planes[9] = {0, 32, 34, 43, 68, 85, 93, 118, 135};
+  return planes[mb] + mb + 45;
 }
 
 // One workgroup: chunk blockIdx.y (of *count) against weight-row tile
@@ -313,9 +340,8 @@ __attribute__((amdgpu_waves_per_eu(2))) void tile_gemm_kernel(
     }
   };
 
-  // ---- dequantization: tile row dr, columns 4 dq .. 4 dq + 3 and +16 for
-  // dq = dq0, dq0 + 1 ----
-  const int dr = tid / 2, dq0 = (tid % 2) * 2;
+  // ---- dequantization: tile row dr, columns j0 .. j0 + 3 of every 8 ----
+  const int dr = tid / 2, j0 = 4 * (tid % 2);
   uint32_t sh_m;  // opaque copy of the sign mask: keeps v_bfi on registers
   asm volatile("" : "=v"(sh_m) : "0"(0x80008000u));
   const int fr = lane & 15, fq = lane >> 4;
@@ -434,17 +460,15 @@ __attribute__((amdgpu_waves_per_eu(2))) void tile_gemm_kernel(
         }
       }
       const uint32_t wd = lds_addr(wtile[dstep & 1]);
-      {  // dq0 even: the two halves of 16-byte chunks dq0 / 2 and 2 + dq0 / 2
-        uint32_t o0[4], o1[4];
-        dequant_pairs<MB, BMIN>(R, b_min, sh_m, dq0, o0);
-        dequant_pairs<MB, BMIN>(R, b_min, sh_m, dq0 + 1, o1);
-        st128(wd + swz(dr, dq0 >> 1), o0[0], o0[1], o1[0], o1[1]);
-        st128(wd + swz(dr, 2 + (dq0 >> 1)), o0[2], o0[3], o1[2], o1[3]);
+      {
+        uint32_t o[8];
+        dequant16<MB, BMIN>(R, b_min, sh_m, j0, o);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) st64(wd + swz(dr, c) + 2 * j0, o[2 * c], o[2 * c + 1]);
       }
       if constexpr (n_mfma > 0) {
-        // one product, then its share of the dequantization's vector
-        // instructions (about 12 per plane and 40 more per step and dq)
-        constexpr int nv = (2 * (12 * MB + 30) + 10 + n_mfma - 1) / n_mfma;
+        // one product, then its share of the dequantization's vector instructions
+        constexpr int nv = (dequant_ops(MB) + n_mfma - 1) / n_mfma;
 #pragma unroll
         for (int i = 0; i < n_mfma; ++i) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);

@@ -30,6 +30,9 @@ CASES = {
     # more, take the LDS-tile GEMM (chunks of 256 positions of one width)
     "tile_200": (2, 8, 64, 320, 64, {4: 200}),
     "tile_two_widths": (5, 8, 128, 256, 128, {5: 420, 8: 1}),
+    # every width on it, for each way of grouping the planes, from b_min 2 and not
+    "tile_widths_from_1": (1, 8, 64, 320, 64, {b: 47 + b for b in range(1, 9)}),
+    "tile_widths_from_2": (2, 8, 128, 256, 128, {b: 53 + b for b in range(2, 9)}),
 }
 
 
