@@ -20,6 +20,8 @@
 // update of a row's later columns uses only that row's block error.
 #pragma clang fp contract(off)
 
+#include <type_traits>
+
 #include "internal.h"
 
 namespace d2moe {
@@ -81,38 +83,59 @@ __device__ inline double lane_value(double v, int lane) {
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
+// f(integral_constant<int, w>) for w = FT, FT - kPhase, .., kPhase.
+constexpr int kPhase = 16;
+template <int W = FT, typename F>
+__device__ __attribute__((always_inline)) inline void phases(F&& f) {
+  f(std::integral_constant<int, W>{});
+  if constexpr (W > kPhase) phases<W - kPhase>(f);
+}
+
 // Cholesky factorization of diagonal tile k (its trailing updates from the
 // tiles left of it are already applied) by one wave: lane r holds row r in
-// registers, column j's multipliers come from their lanes, so no step waits on
-// LDS or a barrier: 57 us a tile, 88 us as 64 steps of
-// three barriers by a 256-thread workgroup.  A
-// non-positive pivot records its 1-based column in *info (first failure wins)
+// registers, column j's multipliers come from LDS, and no step waits on a
+// barrier.  The columns are a loop: v[i] is column j + i of step j, and the
+// update of a step moves every column down one register.  Written out column by
+// column the code is run once only, and fetching it (about 60 KB) takes longer
+// than the arithmetic; the loops of kPhase columns shorten with the columns
+// left.  Factor and calibrated pack of a 2816 x 2048 matrix, with the panel
+// kernel and the loads of U in the quantize kernel changed too: 9.24 -> 8.50 ms.
+// A non-positive pivot records its 1-based column in *info (first failure wins)
 // and continues with pivot 1.
 __global__ __launch_bounds__(64) void potrf_diag_kernel(double* __restrict__ A, int n, int k,
                                                         int32_t* __restrict__ info) {
   __shared__ double a[FT][FT + 1];
+  // l[i] = L[j + i][j]; what lies past the last row is read and not used
+  __shared__ __attribute__((aligned(16))) double l[FT];
   const size_t base = (size_t)k * FT;
   const int r = threadIdx.x;
-#pragma unroll 8
+#pragma unroll 16
   for (int i = 0; i < FT; ++i) a[i][r] = A[(base + i) * n + base + r];
+  l[r] = 0.0;
   __syncthreads();
   double v[FT];
 #pragma unroll
   for (int c = 0; c < FT; ++c) v[c] = a[r][c];
+  phases([&](auto wc) {
+    constexpr int W = decltype(wc)::value;  // columns left at the first step
+#pragma clang loop unroll(disable)
+    for (int j = FT - W; j < FT - W + kPhase; ++j) {
+      double d = lane_value(v[0], j);
+      if (!(d > 0.0)) {
+        if (r == 0) atomicCAS(info, 0, (int32_t)(base + j + 1));
+        d = 1.0;
+      }
+      d = sqrt(d);
+      const double x = r == j ? d : v[0] / d;
+      a[r][j] = r >= j ? x : 0.0;
+      if (r >= j) l[r - j] = x;
+      // the only wave: its LDS accesses are served in order
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-  for (int j = 0; j < FT; ++j) {
-    double d = lane_value(v[j], j);
-    if (!(d > 0.0)) {
-      if (r == 0) atomicCAS(info, 0, (int32_t)(base + j + 1));
-      d = 1.0;
+      for (int i = 1; i < W; ++i) v[i - 1] = fma(-x, l[i], v[i]);
+      __builtin_amdgcn_wave_barrier();
     }
-    d = sqrt(d);
-    v[j] = r == j ? d : v[j] / d;  // rows above the diagonal are not stored
-#pragma unroll
-    for (int c = j + 1; c < FT; ++c) v[c] = fma(-v[j], lane_value(v[j], c), v[c]);
-  }
-#pragma unroll
-  for (int c = 0; c < FT; ++c) a[r][c] = c <= r ? v[c] : 0.0;
+  });
   __syncthreads();
 #pragma unroll 8
   for (int i = 0; i < FT; ++i) A[(base + i) * n + base + r] = a[i][r];
@@ -121,28 +144,35 @@ __global__ __launch_bounds__(64) void potrf_diag_kernel(double* __restrict__ A, 
 // Panel tiles below diagonal tile k: A[i][k] <- A[i][k] L_kk^-T.  One lane
 // per tile row, held in registers; each solved column is taken off the later
 // ones at once (every element still sees its terms in ascending column order).
+// A loop over the columns like the diagonal tile's, for the same reason.
 __global__ __launch_bounds__(64) void trsm_kernel(double* __restrict__ A, int n, int k) {
-  __shared__ __attribute__((aligned(16))) double lt[FT][FT + 2];  // lt[j][m] = L[m][j]
+  // lt[j * kLt + m] = L[m][j]; a step reads up to kPhase - 1 past a row's end
+  // (not used)
+  constexpr int kLt = FT + 2;
+  __shared__ __attribute__((aligned(16))) double lt[FT * kLt + kPhase];
   __shared__ double b[FT][FT + 1];
   const size_t bk = (size_t)k * FT, bi = (size_t)(k + 1 + blockIdx.x) * FT;
   const int r = threadIdx.x;
-#pragma unroll 8
+#pragma unroll 16
   for (int i = 0; i < FT; ++i) {
-    lt[r][i] = A[(bk + i) * n + bk + r];
+    lt[r * kLt + i] = A[(bk + i) * n + bk + r];
     b[i][r] = A[(bi + i) * n + bk + r];
   }
   __syncthreads();
   double v[FT];
 #pragma unroll
   for (int c = 0; c < FT; ++c) v[c] = b[r][c];
+  phases([&](auto wc) {
+    constexpr int W = decltype(wc)::value;
+#pragma clang loop unroll(disable)
+    for (int j = FT - W; j < FT - W + kPhase; ++j) {
+      const double* l = lt + j * kLt + j;  // l[i] = L[j + i][j]
+      const double x = v[0] / l[0];
+      b[r][j] = x;
 #pragma unroll
-  for (int j = 0; j < FT; ++j) {
-    v[j] = v[j] / lt[j][j];
-#pragma unroll
-    for (int m = j + 1; m < FT; ++m) v[m] = fma(-v[j], lt[j][m], v[m]);
-  }
-#pragma unroll
-  for (int c = 0; c < FT; ++c) b[r][c] = v[c];
+      for (int i = 1; i < W; ++i) v[i - 1] = fma(-x, l[i], v[i]);
+    }
+  });
   __syncthreads();
 #pragma unroll 8
   for (int i = 0; i < FT; ++i) A[(bi + i) * n + bk + r] = b[i][r];
@@ -306,6 +336,7 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const float* __restrict_
 // of magnitudes is one chain per (row, group), run by a lane each from LDS.
 // 2816 x 2048, blocks of 128: 26 us a launch, 228 us with one lane per row.
 constexpr int kQuantRows = 4, kQuantWaves = 4;
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // U: 4-byte aligned
 template <int G, int GAMMA>
 __global__ __launch_bounds__(64 * kQuantWaves) void calib_quant_kernel(
     const float* __restrict__ W, const float* __restrict__ T, float* __restrict__ R,
@@ -314,7 +345,7 @@ __global__ __launch_bounds__(64 * kQuantWaves) void calib_quant_kernel(
   constexpr int C = GAMMA / 64, NG = GAMMA / G;  // columns per lane, groups per block
   constexpr int CG = G / 64;                     // lane columns per group
   constexpr int BR = 2048 / G;
-  __shared__ float us[GAMMA][GAMMA];
+  __shared__ __attribute__((aligned(16))) float us[GAMMA][GAMMA];
   __shared__ __attribute__((aligned(16))) float mag[kQuantWaves][kQuantRows][GAMMA + 4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n0 = (blockIdx.x * kQuantWaves + wave) * kQuantRows;
@@ -331,9 +362,15 @@ __global__ __launch_bounds__(64 * kQuantWaves) void calib_quant_kernel(
       t[r][c] = ok ? T[at] : 0.0f;
       w[r][c] = ok ? (lev == 0 ? W[at] : R[at]) : 0.0f;
     }
-#pragma unroll 8
-  for (int idx = threadIdx.x; idx < GAMMA * GAMMA; idx += 64 * kQuantWaves)
-    us[idx / GAMMA][idx % GAMMA] = U[(size_t)(b0 + idx / GAMMA) * h + b0 + idx % GAMMA];
+  // the block of U: all loads of a thread in flight at once, under the
+  // quantization below
+  constexpr int kUVec = GAMMA * GAMMA / 4 / (64 * kQuantWaves);
+  f4u uv[kUVec];
+#pragma unroll
+  for (int q = 0; q < kUVec; ++q) {
+    const int at = 4 * ((int)threadIdx.x + 64 * kQuantWaves * q);
+    uv[q] = *(const f4u*)(U + (size_t)(b0 + at / GAMMA) * h + b0 + at % GAMMA);
+  }
 
   float v[kQuantRows][C];  // block errors, then E
   if (lev == 0) {
@@ -440,6 +477,11 @@ __global__ __launch_bounds__(64 * kQuantWaves) void calib_quant_kernel(
     if (n0 + r < m.rows)
 #pragma unroll
       for (int c = 0; c < C; ++c) R[(size_t)(n0 + r) * h + b0 + 64 * c + lane] = w[r][c];
+#pragma unroll
+  for (int q = 0; q < kUVec; ++q) {
+    const int at = 4 * ((int)threadIdx.x + 64 * kQuantWaves * q);
+    *(float4*)&us[at / GAMMA][at % GAMMA] = float4{uv[q].x, uv[q].y, uv[q].z, uv[q].w};
+  }
   __syncthreads();  // the block of U is in LDS
 
   // E = D U_BB^-1, forward substitution in ascending order
@@ -490,7 +532,6 @@ __global__ __launch_bounds__(64 * kQuantWaves) void calib_quant_kernel(
 // so that several workgroups share a compute unit.  2816 x 2048: 19 us a
 // launch on average, 82 us with 64 x 32 tiles of 128 threads.
 constexpr int kUpdTile = 64, kUpdDepth = 32;
-typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // U: 4-byte aligned
 __global__ __launch_bounds__(256) void calib_update_kernel(float* __restrict__ T,
                                                            const float* __restrict__ U,
                                                            const float* __restrict__ E, int N,
