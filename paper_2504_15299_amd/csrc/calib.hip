@@ -98,8 +98,7 @@ __device__ __attribute__((always_inline)) inline void phases(F&& f) {
 // update of a step moves every column down one register.  Written out column by
 // column the code is run once only, and fetching it (about 60 KB) takes longer
 // than the arithmetic; the loops of kPhase columns shorten with the columns
-// left.  Factor and calibrated pack of a 2816 x 2048 matrix, with the panel
-// kernel and the loads of U in the quantize kernel changed too: 9.24 -> 8.50 ms.
+// left: 57 -> 31 us a tile.
 // A non-positive pivot records its 1-based column in *info (first failure wins)
 // and continues with pivot 1.
 __global__ __launch_bounds__(64) void potrf_diag_kernel(double* __restrict__ A, int n, int k,
@@ -143,36 +142,31 @@ __global__ __launch_bounds__(64) void potrf_diag_kernel(double* __restrict__ A, 
 
 // Panel tiles below diagonal tile k: A[i][k] <- A[i][k] L_kk^-T.  One lane
 // per tile row, held in registers; each solved column is taken off the later
-// ones at once (every element still sees its terms in ascending column order).
-// A loop over the columns like the diagonal tile's, for the same reason.
+// ones at once (every element still sees its terms in ascending column order).  Written out,
+// unlike the diagonal tile: 23 us a launch, 32 as loops of kPhase columns, as its
+// workgroups share the instructions and a loop waits for its LDS reads.
 __global__ __launch_bounds__(64) void trsm_kernel(double* __restrict__ A, int n, int k) {
-  // lt[j * kLt + m] = L[m][j]; a step reads up to kPhase - 1 past a row's end
-  // (not used)
-  constexpr int kLt = FT + 2;
-  __shared__ __attribute__((aligned(16))) double lt[FT * kLt + kPhase];
+  __shared__ __attribute__((aligned(16))) double lt[FT][FT + 2];  // lt[j][m] = L[m][j]
   __shared__ double b[FT][FT + 1];
   const size_t bk = (size_t)k * FT, bi = (size_t)(k + 1 + blockIdx.x) * FT;
   const int r = threadIdx.x;
-#pragma unroll 16
+#pragma unroll 8
   for (int i = 0; i < FT; ++i) {
-    lt[r * kLt + i] = A[(bk + i) * n + bk + r];
+    lt[r][i] = A[(bk + i) * n + bk + r];
     b[i][r] = A[(bi + i) * n + bk + r];
   }
   __syncthreads();
   double v[FT];
 #pragma unroll
   for (int c = 0; c < FT; ++c) v[c] = b[r][c];
-  phases([&](auto wc) {
-    constexpr int W = decltype(wc)::value;
-#pragma clang loop unroll(disable)
-    for (int j = FT - W; j < FT - W + kPhase; ++j) {
-      const double* l = lt + j * kLt + j;  // l[i] = L[j + i][j]
-      const double x = v[0] / l[0];
-      b[r][j] = x;
 #pragma unroll
-      for (int i = 1; i < W; ++i) v[i - 1] = fma(-x, l[i], v[i]);
-    }
-  });
+  for (int j = 0; j < FT; ++j) {
+    v[j] = v[j] / lt[j][j];
+#pragma unroll
+    for (int m = j + 1; m < FT; ++m) v[m] = fma(-v[j], lt[j][m], v[m]);
+  }
+#pragma unroll
+  for (int c = 0; c < FT; ++c) b[r][c] = v[c];
   __syncthreads();
 #pragma unroll 8
   for (int i = 0; i < FT; ++i) A[(bi + i) * n + bk + r] = b[i][r];
@@ -334,7 +328,8 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const float* __restrict_
 // U's row from LDS, so a column costs one step instead of j dependent ones.
 // Every element still sees its terms in ascending column order.  Only the sum
 // of magnitudes is one chain per (row, group), run by a lane each from LDS.
-// 2816 x 2048, blocks of 128: 26 us a launch, 228 us with one lane per row.
+// 2816 x 2048, blocks of 128: 24 us a launch (26 with U in rounds of 4-byte
+// loads, 228 with one lane per row).
 constexpr int kQuantRows = 4, kQuantWaves = 4;
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // U: 4-byte aligned
 template <int G, int GAMMA>
