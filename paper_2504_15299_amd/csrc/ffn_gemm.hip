@@ -620,30 +620,75 @@ __global__ void to_bf16_kernel(const float* __restrict__ in, size_t n, uint16_t*
 }
 
 // out[t][c] = sum_i w[t][i] * y[slot_of[t*k+i]][c] (+ the shared expert's
-// output, the sum of its ys_parts partial planes), i ascending.
-template <typename TOUT>
-__global__ void combine_kernel(const float* __restrict__ y, const float* __restrict__ ys,
-                               int ys_parts, size_t ys_split, const float* __restrict__ topk_w,
-                               const int32_t* __restrict__ slot_of, int k, int d,
-                               TOUT* __restrict__ out) {
+// output, the sum of its ys_parts partial planes), i ascending.  Four columns
+// per thread, and the rows' loads are issued AHEAD (the power of two that holds
+// k, at most 8) at a time before their sums: memory latency bounds it at one column and one load in flight.
+// 2048 tokens of 4096, top-2: 31 -> 14.5 us; 512 tokens of 2048, top-6 with a
+// shared expert: 15.5 -> 12.2; one token of 4096: 4.7 -> 4.4.
+constexpr int kCombineThreads = 128;
+template <typename TOUT, int AHEAD>
+__global__ __launch_bounds__(kCombineThreads) void combine_kernel(
+    const float* __restrict__ y, const float* __restrict__ ys, int ys_parts, size_t ys_split,
+    const float* __restrict__ topk_w, const int32_t* __restrict__ slot_of, int k, int d,
+    TOUT* __restrict__ out) {
   const int t = blockIdx.y;
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= d) return;
-  float acc = 0.0f;
-  for (int i = 0; i < k; ++i) {
-    const int pos = slot_of[t * k + i];
-    acc += topk_w[t * k + i] * y[(size_t)pos * d + c];
+  const int c = 4 * (blockIdx.x * blockDim.x + threadIdx.x);
+  if (c >= d) return;  // d % 64 == 0
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int i0 = 0; i0 < k; i0 += AHEAD) {
+    f32x4 v[AHEAD];
+    float w[AHEAD];
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) {  // past the last row: it again, not summed
+      const int at = t * k + min(i0 + i, k - 1);
+      v[i] = *(const f32x4*)(y + (size_t)slot_of[at] * d + c);
+      w[i] = topk_w[at];
+    }
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i)
+      if (i0 + i < k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += w[i] * v[i][e];
   }
   if (ys) {
     // the shared expert's reduction parts, summed in order
-    float sh = 0.0f;
-    for (int z = 0; z < ys_parts; ++z) sh += ys[(size_t)z * ys_split + (size_t)t * d + c];
+    f32x4 sh = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int z = 0; z < ys_parts; ++z) sh += *(const f32x4*)(ys + z * ys_split + (size_t)t * d + c);
     acc += sh;
   }
-  if constexpr (sizeof(TOUT) == 2)
-    out[(size_t)t * d + c] = f2bf(acc);
-  else
-    out[(size_t)t * d + c] = acc;
+  // the caller's buffer: aligned to its elements only
+  typedef TOUT out4 __attribute__((ext_vector_type(4), aligned(sizeof(TOUT))));
+  out4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (sizeof(TOUT) == 2)
+      o[e] = f2bf(acc[e]);
+    else
+      o[e] = acc[e];
+  }
+  *(out4*)(out + (size_t)t * d + c) = o;
+}
+hipError_t launch_combine(const float* y, const float* ys, int ys_parts, size_t ys_split,
+                          const d2moe_routing* r, int T, int k, int d, d2moe_dtype xd, void* out,
+                          hipStream_t s) {
+  const int quads = d / 4, threads = quads < kCombineThreads ? (quads + 63) / 64 * 64 : kCombineThreads;
+  const dim3 grid((quads + threads - 1) / threads, T);
+  auto launch = [&](auto ahead) {
+    constexpr int A = decltype(ahead)::value;
+    if (xd == D2MOE_BF16)
+      combine_kernel<uint16_t, A><<<grid, threads, 0, s>>>(y, ys, ys_parts, ys_split, r->topk_w,
+                                                           r->slot_of, k, d, (uint16_t*)out);
+    else
+      combine_kernel<float, A><<<grid, threads, 0, s>>>(y, ys, ys_parts, ys_split, r->topk_w,
+                                                        r->slot_of, k, d, (float*)out);
+  };
+  using std::integral_constant;
+  k <= 1   ? launch(integral_constant<int, 1>{})
+  : k <= 2 ? launch(integral_constant<int, 2>{})
+  : k <= 4 ? launch(integral_constant<int, 4>{})
+           : launch(integral_constant<int, 8>{});
+  return hipGetLastError();
 }
 
 // One matrix's share of a nested delta: per packed block, planes [p0, p1) and
@@ -1036,14 +1081,7 @@ hipError_t launch_forward_streamed(const void* x, d2moe_dtype xd, int T, int d, 
     if (err != hipSuccess) return err;
   }
   if (T == 0) return hipSuccess;
-  dim3 cg((d + 255) / 256, T);
-  if (xd == D2MOE_BF16)
-    combine_kernel<uint16_t><<<cg, 256, 0, s>>>(y, nullptr, 1, 0, r->topk_w, r->slot_of, k, d,
-                                                (uint16_t*)out);
-  else
-    combine_kernel<float><<<cg, 256, 0, s>>>(y, nullptr, 1, 0, r->topk_w, r->slot_of, k, d,
-                                             (float*)out);
-  return hipGetLastError();
+  return launch_combine(y, nullptr, 1, 0, r, T, k, d, xd, out, s);
 }
 
 hipError_t launch_forward(const void* x, d2moe_dtype xd, int T, int d, int d_ff, int E, int k,
@@ -1144,16 +1182,8 @@ hipError_t launch_forward(const void* x, d2moe_dtype xd, int T, int d, int d_ff,
   }
   if (fork_shared && (err = hipStreamWaitEvent(s, side->join, 0)) != hipSuccess) return err;
 
-  dim3 cg((d + 255) / 256, T);
-  if (xd == D2MOE_BF16)
-    combine_kernel<uint16_t><<<cg, 256, 0, s>>>(y, has_shared ? ys : nullptr, L.shared_ksplit,
-                                                (size_t)T * d, r->topk_w, r->slot_of, k, d,
-                                                (uint16_t*)out);
-  else
-    combine_kernel<float><<<cg, 256, 0, s>>>(y, has_shared ? ys : nullptr, L.shared_ksplit,
-                                             (size_t)T * d, r->topk_w, r->slot_of, k, d,
-                                             (float*)out);
-  return hipGetLastError();
+  return launch_combine(y, has_shared ? ys : nullptr, L.shared_ksplit, (size_t)T * d, r, T, k, d, xd,
+                        out, s);
 }
 
 }  // namespace d2moe
