@@ -85,13 +85,26 @@ struct GemmWork {
 //
 // Longest workgroups first: experts (buckets) of the largest bit-width, then of
 // the most positions.  One workgroup of kChunkThreads threads, one per expert
-// (E <= 64) and one per bucket (E L <= 512).
+// (E <= 64) and one per bucket (E L <= 512).  Workgroups past the first round n
+// values of x to bf16 in xb instead: neither needs the other, and a launch of
+// its own takes 2 us of a small fp32 layer's 45 (64 tokens of 256, d_ff 512).
 __host__ __device__ inline bool on_tiles(int tiles, int reg) { return 17 * tiles < 10 * reg; }
 constexpr int kChunkThreads = 512;
 constexpr int kTileAverage = 384;
+constexpr int kConvert = 4;  // values per thread
 __global__ __launch_bounds__(kChunkThreads) void chunk_kernel(
     const int32_t* __restrict__ hist, const int32_t* __restrict__ offsets, int E, int L, int b_min,
-    int slots, bool all_tile, int32_t* __restrict__ table) {
+    int slots, bool all_tile, int32_t* __restrict__ table, const float* __restrict__ x, size_t n,
+    uint16_t* __restrict__ xb) {
+  if (blockIdx.x > 0) {  // workgroup-uniform
+    const size_t i0 = (size_t)(blockIdx.x - 1) * (kChunkThreads * kConvert) + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < kConvert; ++i) {
+      const size_t at = i0 + i * kChunkThreads;
+      if (at < n) xb[at] = f2bf(x[at]);
+    }
+    return;
+  }
   __shared__ int rkey[64], nreg[64], on_tile[64];
   __shared__ int tkey[kChunkThreads], ntile[kChunkThreads];
   const int j = threadIdx.x;
@@ -130,9 +143,9 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_kernel(
     return;
   }
   const int nb = E * L;
-  const int n = j < nb && on_tile[j / L] ? hist[j] : 0;
-  ntile[j] = (n + kTileChunk - 1) / kTileChunk;
-  tkey[j] = n > 0 ? ((j % L + 1) << 24) + min(n, (1 << 24) - 1) : 0;
+  const int cnt = j < nb && on_tile[j / L] ? hist[j] : 0;
+  ntile[j] = (cnt + kTileChunk - 1) / kTileChunk;
+  tkey[j] = cnt > 0 ? ((j % L + 1) << 24) + min(cnt, (1 << 24) - 1) : 0;
   __syncthreads();
   total = first = 0;
   for (int o = 0; o < nb; ++o) {
@@ -143,7 +156,7 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_kernel(
   for (int c = 0; c < ntile[j]; ++c) {
     int32_t* t = table + 4 * (slots - 1 - first - c);
     t[0] = offsets[j] + c * kTileChunk;
-    t[1] = min(kTileChunk, n - c * kTileChunk);
+    t[1] = min(kTileChunk, cnt - c * kTileChunk);
     t[2] = b_min + j % L;
     t[3] = j / L;
   }
@@ -849,11 +862,13 @@ int chunk_estimate(int T, int k, int E) {
   return (E < T * k ? E : T * k) + T * k / (2 * kBlocks * kBlockPos);
 }
 
-// Slots of four words of the chunk table: one per bucket and one per 256
-// positions.  An expert's register chunks are no more than its tile chunks
-// wherever it takes the former, so both tables together have at most
-// sum (m + 255) / 256 entries over the buckets of m positions, and at least
-// one slot is left for the counts.
+// Slots of four words of the chunk table: one per bucket (nb = 8 E, or n if
+// fewer) and one per 256 positions.  Where every expert takes the tile GEMM, a
+// bucket of m positions has (m + 255) / 256 chunks, and one slot is left for the
+// counts.  Otherwise n < kTileAverage E; m positions of an expert in l buckets
+// make at most m / 128 + l / 8 + 1 register chunks, and l tile chunks only from
+// about 200 l positions on: at most n / 113 + 1.9 E + 1 slots in all, below
+// 8 E.  With n < 8 E, an expert has at most a chunk per position.
 int chunk_room(int n, int nb) { return (nb < n ? nb : n) + (n + 255) / 256; }
 
 // The shared expert is one bucket of T positions, on the tile GEMM from here
@@ -898,8 +913,9 @@ hipError_t run_gemm_g(const uint16_t* in, int in_ld, const int32_t* perm, int kd
   // of the GPU's 512 places for them (n_wg: about as many as there will be) and
   // each group still has a few steps.  Mixtral shape, ms per step in one group /
   // two: 70 tokens (256 workgroups of 112 steps) 0.99 / 0.93, 301 (320) 1.14 /
-  // 1.06, 512 (384) 1.31 / 1.35.
-  const bool two = !SWIGLU && n_wg <= 352 && W.cols / kStepK / ksplit >= 8;
+  // 1.06, 512 (384) 1.31 / 1.35.  At four steps (d_ff 512, 64 tokens of 256) the
+  // launch takes 16.5 / 14.5 us.
+  const bool two = !SWIGLU && n_wg <= 352 && W.cols / kStepK / ksplit >= 4;
   auto launch = [&](auto kernel, int threads) {
     kernel<<<grid, threads, 0, s>>>(in, in_ld, perm, kdiv, W, wk, tiles, N, N, out, out_ld,
                                     out_split);
@@ -1101,13 +1117,16 @@ hipError_t launch_forward(const void* x, d2moe_dtype xd, int T, int d, int d_ff,
   float* ys = (float*)(base + L.ys_off);
   // bf16 activations for the grouped GEMM (fp32 inputs are rounded once)
   const uint16_t* xb = (const uint16_t*)x;
-  const bool gemm_needed = has_shared || !decode_path_ok(w13, w2, T);
-  if (xd == D2MOE_F32 && gemm_needed) {
-    uint16_t* xw = (uint16_t*)(base + L.xb_off);
-    const size_t n = (size_t)T * d;
-    to_bf16_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>((const float*)x, n, xw);
-    hipError_t e0 = hipGetLastError();
-    if (e0 != hipSuccess) return e0;
+  const bool decode = decode_path_ok(w13, w2, T);
+  const bool convert = xd == D2MOE_F32 && (has_shared || !decode);
+  const size_t n = (size_t)T * d;
+  uint16_t* xw = (uint16_t*)(base + L.xb_off);
+  if (convert) {
+    if (has_shared) {  // both chains read it; otherwise the chunk tables' launch writes it
+      to_bf16_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>((const float*)x, n, xw);
+      hipError_t e0 = hipGetLastError();
+      if (e0 != hipSuccess) return e0;
+    }
     xb = xw;
   }
 
@@ -1115,7 +1134,6 @@ hipError_t launch_forward(const void* x, d2moe_dtype xd, int T, int d, int d_ff,
   // Concurrency: the shared expert's chain runs on a side stream forked from
   // `s` (it writes its own workspace, hs / ys); the combine waits for it.  Not
   // with events: those time the kernels on `s`.
-  const bool decode = decode_path_ok(w13, w2, T);
   const bool fork_shared = concurrent && !events && has_shared;
   SideStream* side = nullptr;
   if (fork_shared && (err = side_stream(&side)) != hipSuccess) return err;
@@ -1157,8 +1175,11 @@ hipError_t launch_forward(const void* x, d2moe_dtype xd, int T, int d, int d_ff,
     if (err != hipSuccess) return err;
   } else {
     const bool all_tile = (long)T * k >= (long)kTileAverage * E;
-    chunk_kernel<<<1, kChunkThreads, 0, s>>>(r->hist, r->offsets, E, Lv, w13->b_min, L.chunk_n,
-                                            all_tile, table);
+    constexpr int kPer = kChunkThreads * kConvert;
+    const unsigned conv = convert && !has_shared ? (unsigned)((n + kPer - 1) / kPer) : 0;
+    chunk_kernel<<<1 + conv, kChunkThreads, 0, s>>>(r->hist, r->offsets, E, Lv, w13->b_min,
+                                                    L.chunk_n, all_tile, table, (const float*)x, n,
+                                                    xw);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     const int n_ub = all_tile ? 0 : chunk_bound(T * k, Lv, E);
     // an expert holds at most T positions, one per token
