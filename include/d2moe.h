@@ -411,6 +411,11 @@ d2moe_status d2moe_budget_plan(const uint8_t* want, int32_t n_layers, int32_t E,
  * arithmetic is that of d2moe_moe_forward's grouped-GEMM path (more than 64
  * tokens), whatever the batch.  Both streams are the caller's; the call
  * returns after enqueueing.
+ * Order: the copies start after everything enqueued on `stream` before the
+ * call (`io_stream` waits for it once, by way of events[0]), so the device
+ * copy may be new memory of `stream` or be read by work that is still queued
+ * there; `stream` waits for every copy of the call before its own later work.
+ * The host copy must stay as it is until the copies are done.
  */
 d2moe_status d2moe_moe_forward_streamed(
     const void* x, d2moe_dtype x_dtype, int32_t T, int32_t d, int32_t d_ff, int32_t E, int32_t k,

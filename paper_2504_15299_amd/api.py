@@ -446,7 +446,8 @@ def moe_forward_streamed(x, host_w13: MWQ, host_w2: MWQ, w13: MWQ, w2: MWQ, resi
     """``d2moe_moe_forward_streamed``: host_w13 / host_w2 hold pinned host
     tensors, w13 / w2 the device copy; resident is a host uint8 numpy array
     [E] (updated in place); units as returned by hebf_order; events: one
-    torch.cuda.Event per unit; io_stream: a torch.cuda.Stream."""
+    torch.cuda.Event per unit; io_stream: a torch.cuda.Stream, which waits for
+    the work already on ``stream`` before its first copy."""
     import numpy as np
     T, d = x.shape
     E, d_ff = w13.n_experts, w2.cols

@@ -1035,6 +1035,16 @@ hipError_t launch_forward_streamed(const void* x, d2moe_dtype xd, int T, int d, 
   uint16_t* h = (uint16_t*)(base + L.h_off);
   float* y = (float*)(base + L.y_off);
   hipError_t err;
+  // The copies follow what `s` holds already: work that reads the device copy
+  // or still uses its memory (a fill, or a temporary that was there before).
+  // events[0] carries that order and is recorded again for its unit below; a
+  // wait keeps the record that it was enqueued after.
+  bool loads = false;
+  for (int i = 0; i < n_units; ++i) loads |= units[i].load_to > units[i].load_from;
+  if (loads) {
+    if ((err = hipEventRecord(events[0], s)) != hipSuccess) return err;
+    if ((err = hipStreamWaitEvent(io, events[0], 0)) != hipSuccess) return err;
+  }
   const uint16_t* xb = (const uint16_t*)x;
   if (T > 0 && xd == D2MOE_F32) {
     uint16_t* xw = (uint16_t*)(base + L.xb_off);
