@@ -65,37 +65,79 @@ struct GemmWork {
   int one_first, one_cnt, one_bits, one_expert, one_blocks;
 };
 
-// Chunk tables of both GEMMs from the routing histogram, in `slots` slots of four
-// words: slot 0 = {register chunks, tile chunks}; the register chunks from slot
-// 1 up, {expert | blocks << 8, first block of the expert}; the tile chunks from
-// the last slot down, {first position, positions, bit-width, expert}.
-//
-// Register chunks: an expert's blocks, all bit-widths together, in as few
-// chunks of at most kBlocks as hold them, of even size.  Tile chunks: the
-// positions of each bucket in chunks of kTileChunk.  Each chunk dequantizes the
-// expert's weights once, so an expert takes the tile GEMM (whose chunks hold
-// 256 positions, but of one bit-width) where that makes 1.7 times fewer chunks,
-// about what a tile chunk costs in register chunks: 192 positions per expert of
-// one width (64 experts, group 64) are one chunk or two, 0.73 ms per step
-// against 0.93; 128 per expert at the Mixtral shape with widths 2, 4, 8 and
-// Zipf load 1.31 ms, 1.71 with its two largest experts on tiles.  From
-// kTileAverage positions per expert every expert takes the tile GEMM
-// (`all_tile`), in one launch: at 512 per expert 2.77 ms with that load, 3.06
-// with the small experts on the register GEMM, 3.11 with all of them on it.
+// Chunks of one expert with n[l] positions at the l-th bit-width.
+// Register chunks: the expert's blocks, all bit-widths together, in as few
+// chunks of at most kBlocks as hold them.  Tile chunks: the positions of each
+// bucket in chunks of kTileChunk.
+struct ChunkCount {
+  int reg, cost, tiles;  // cost: of the register chunks (use_tiles)
+  __host__ __device__ void add(const ChunkCount& o) {
+    reg += o.reg, cost += o.cost, tiles += o.tiles;
+  }
+};
+__host__ __device__ inline int expert_blocks(const int32_t* n, int L, int b_min, ChunkCount* c) {
+  int blocks = 0, widths = 0, top = 0;
+  for (int l = 0; l < L; ++l) {
+    blocks += (n[l] + kBlockPos - 1) / kBlockPos;
+    c->tiles += (n[l] + kTileChunk - 1) / kTileChunk;
+    widths += n[l] > 0;
+    if (n[l] > 0) top = b_min + l;
+  }
+  const int reg = (blocks + kBlocks - 1) / kBlocks;
+  c->reg += reg;
+  c->cost += reg * (24 + top + 4 * widths);
+  return blocks;
+}
+
+// Whether the layer's routed experts take the tile GEMM (all of them: with some
+// on each, the two launches follow one another, each with its own tail, and at
+// 8 experts of d 4096, d_ff 4096, one width of 4 bits, 130 positions per expert
+// a step took 392 us with half of them on tiles, 280 on registers, 283 on tiles).
+// A chunk dequantizes 128 rows, once for up to 256 positions of one width (tile)
+// or 128 of any (register).  A register chunk of w widths up to b bits takes
+// about (24 + b + 4 w) / 48 of a tile chunk's time; 512 workgroups run at once,
+// so fewer than that take the time of one.  Fitted to 1568 layers (E 1 to 64, d
+// 512 to 5120, 40 to 380 positions per expert, one to seven widths, even and Zipf
+// load): 0.3 % above the faster GEMM on average, tile / register, us per step: 8
+// experts of d 4096, d_ff 14336, 260 per expert, 8 bits 1651 / 2145 (tile), 4
+// bits 1368 / 1358 and widths 2, 4, 8 2207 / 2121 (register); 4 experts of d 1024,
+// d_ff 2048, 260 per expert, 4 bits 115 / 86 (register: 224 workgroups); 16 of d
+// 2048, d_ff 1408, Zipf load, 180 per expert, each of one width, 176 / 208 (tile).
+// From kTileAverage positions per expert on it is tiles whatever the counts, so
+// that the register launch is left out.
+constexpr int kTileAverage = 384;
+// Bound on the tile chunks of a layer of T tokens, top-k, that would make at most
+// `reg` register chunks; at 0 the tile launch is left out.  use_tiles keeps to it,
+// which excludes nothing that the costs favour: with at most 128 tokens, and so
+// positions per expert, there are no fewer tile chunks than register chunks, and
+// the costs need 30 positions or more per tile chunk.
+__host__ __device__ inline int tile_bound(int T, int k, int reg) {
+  if (T <= kBlocks * kBlockPos) return 0;
+  return T * k / 29 < reg ? T * k / 29 : reg - 1;
+}
+__host__ __device__ inline bool use_tiles(const ChunkCount& c, int row_tiles, int T, int k) {
+  if (c.tiles > tile_bound(T, k, c.reg)) return false;
+  const long reg = (long)c.reg * row_tiles, tiles = (long)c.tiles * row_tiles;
+  return c.cost * (reg > 512 ? reg : 512) > 48l * c.reg * (tiles > 512 ? tiles : 512);
+}
+
+// Chunk table of the layer's GEMM from the routing histogram, in slots of four
+// words: slot 0 = {register chunks, tile chunks}, one of them 0; then the chunks,
+// a register chunk as {expert | blocks << 8, first block of the expert} (an
+// expert's chunks are of even size), a tile chunk as {first position, positions,
+// bit-width, expert}.  row_tiles: workgroups of W1/W3 per chunk.
 //
 // Longest workgroups first: experts (buckets) of the largest bit-width, then of
 // the most positions.  One workgroup of kChunkThreads threads, one per expert
 // (E <= 64) and one per bucket (E L <= 512).  Workgroups past the first round n
 // values of x to bf16 in xb instead: neither needs the other, and a launch of
 // its own takes 2 us of a small fp32 layer's 45 (64 tokens of 256, d_ff 512).
-__host__ __device__ inline bool on_tiles(int tiles, int reg) { return 17 * tiles < 10 * reg; }
 constexpr int kChunkThreads = 512;
-constexpr int kTileAverage = 384;
 constexpr int kConvert = 4;  // values per thread
 __global__ __launch_bounds__(kChunkThreads) void chunk_kernel(
     const int32_t* __restrict__ hist, const int32_t* __restrict__ offsets, int E, int L, int b_min,
-    int slots, bool all_tile, int32_t* __restrict__ table, const float* __restrict__ x, size_t n,
-    uint16_t* __restrict__ xb) {
+    int row_tiles, int T, int k, bool all_tile, int32_t* __restrict__ table,
+    const float* __restrict__ x, size_t n, uint16_t* __restrict__ xb) {
   if (blockIdx.x > 0) {  // workgroup-uniform
     const size_t i0 = (size_t)(blockIdx.x - 1) * (kChunkThreads * kConvert) + threadIdx.x;
 #pragma unroll
@@ -105,56 +147,59 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_kernel(
     }
     return;
   }
-  __shared__ int rkey[64], nreg[64], on_tile[64];
+  __shared__ int rkey[64];
+  __shared__ ChunkCount count[64];
   __shared__ int tkey[kChunkThreads], ntile[kChunkThreads];
   const int j = threadIdx.x;
-  int tot = 0, mb = 0, tiles = 0;
+  int tot = 0;
   if (j < E) {
+    int n[8], mb = 0;
 #pragma unroll
     for (int l = 0; l < 8; ++l) {
-      const int n = l < L ? hist[j * L + l] : 0;
-      tot += (n + kBlockPos - 1) / kBlockPos;
-      tiles += (n + kTileChunk - 1) / kTileChunk;
-      if (n > 0) mb = l + 1;
+      n[l] = l < L ? hist[j * L + l] : 0;
+      if (n[l] > 0) mb = l + 1;
     }
-    const int reg = (tot + kBlocks - 1) / kBlocks;
-    const bool tile = all_tile || on_tiles(tiles, reg);
-    on_tile[j] = tile;
+    ChunkCount c{};
+    tot = expert_blocks(n, 8, b_min, &c);
+    count[j] = c;
     rkey[j] = (mb << 24) + min(tot, (1 << 24) - 1);
-    nreg[j] = tile ? 0 : reg;
   }
-  const int any_tile = __syncthreads_or(j < E && on_tile[j]);
-  int total = 0, first = 0;
+  __syncthreads();
+  ChunkCount sum{};
+  int first = 0;
   for (int o = 0; o < E; ++o) {
-    total += nreg[o];
-    if (j < E && (rkey[o] > rkey[j] || (rkey[o] == rkey[j] && o < j))) first += nreg[o];
+    sum.add(count[o]);
+    if (j < E && (rkey[o] > rkey[j] || (rkey[o] == rkey[j] && o < j))) first += count[o].reg;
   }
-  if (j == 0) table[0] = total;
-  if (j < E) {
-    const int nc = nreg[j];
-    for (int c = 0; c < nc; ++c) {
-      const int b0 = (int)((long)c * tot / nc), b1 = (int)((long)(c + 1) * tot / nc);
-      table[4 * (1 + first + c)] = j | (b1 - b0) << 8;
-      table[4 * (1 + first + c) + 1] = b0;
+  if (!all_tile && !use_tiles(sum, row_tiles, T, k)) {  // workgroup-uniform
+    if (j == 0) {
+      table[0] = sum.reg;
+      table[1] = 0;
     }
-  }
-  if (!any_tile) {  // workgroup-uniform
-    if (j == 0) table[1] = 0;
+    if (j < E) {
+      const int nc = count[j].reg;
+      for (int c = 0; c < nc; ++c) {
+        const int b0 = (int)((long)c * tot / nc), b1 = (int)((long)(c + 1) * tot / nc);
+        table[4 * (1 + first + c)] = j | (b1 - b0) << 8;
+        table[4 * (1 + first + c) + 1] = b0;
+      }
+    }
     return;
   }
   const int nb = E * L;
-  const int cnt = j < nb && on_tile[j / L] ? hist[j] : 0;
+  const int cnt = j < nb ? hist[j] : 0;
   ntile[j] = (cnt + kTileChunk - 1) / kTileChunk;
   tkey[j] = cnt > 0 ? ((j % L + 1) << 24) + min(cnt, (1 << 24) - 1) : 0;
   __syncthreads();
-  total = first = 0;
-  for (int o = 0; o < nb; ++o) {
-    total += ntile[o];
+  first = 0;
+  for (int o = 0; o < nb; ++o)
     if (tkey[o] > tkey[j] || (tkey[o] == tkey[j] && o < j)) first += ntile[o];
+  if (j == 0) {
+    table[0] = 0;
+    table[1] = sum.tiles;
   }
-  if (j == 0) table[1] = total;
   for (int c = 0; c < ntile[j]; ++c) {
-    int32_t* t = table + 4 * (slots - 1 - first - c);
+    int32_t* t = table + 4 * (1 + first + c);
     t[0] = offsets[j] + c * kTileChunk;
     t[1] = min(kTileChunk, cnt - c * kTileChunk);
     t[2] = b_min + j % L;
@@ -840,20 +885,13 @@ hipError_t copy_delta(const d2moe_mwq* hm, const d2moe_mwq* dm, int e, int from,
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Bounds on the register and the tile chunks that n positions in at most L
-// buckets of each of E experts can make.  A bucket of m positions has at most
-// (m + 15) / 16 blocks, an expert of t blocks at most (t + 7) / 8 register
-// chunks; unless all do, only experts of more than 128 positions take the tile
-// GEMM, with fewer chunks than their blocks would make.
+// Bound on the register chunks that n positions in at most L buckets of each of
+// E experts can make.  A bucket of m positions has at most (m + 15) / 16 blocks,
+// an expert of t blocks at most (t + 7) / 8 register chunks.
 int chunk_bound(int n, int L, int E) {
   const long experts = E < n ? E : n, buckets = (long)E * L < n ? (long)E * L : n;
   const long blocks = (n + (kBlockPos - 1) * buckets) / kBlockPos;
   return (int)((blocks + (kBlocks - 1) * experts) / kBlocks);
-}
-int tile_bound(int n, int L, int E) {
-  const long large = n / (kBlocks * kBlockPos + 1);
-  const long experts = large < E ? large : E;
-  return (int)((n / kBlockPos + L * experts) / kBlocks);
 }
 
 // About how many register chunks there will be: one per active expert and one
@@ -863,12 +901,12 @@ int chunk_estimate(int T, int k, int E) {
 }
 
 // Slots of four words of the chunk table: one per bucket (nb = 8 E, or n if
-// fewer) and one per 256 positions.  Where every expert takes the tile GEMM, a
-// bucket of m positions has (m + 255) / 256 chunks, and one slot is left for the
-// counts.  Otherwise n < kTileAverage E; m positions of an expert in l buckets
-// make at most m / 128 + l / 8 + 1 register chunks, and l tile chunks only from
-// about 200 l positions on: at most n / 113 + 1.9 E + 1 slots in all, below
-// 8 E.  With n < 8 E, an expert has at most a chunk per position.
+// fewer) and one per 256 positions.  Where every expert takes the tile GEMM by
+// the average, a bucket of m positions has (m + 255) / 256 chunks, and one slot
+// is left for the counts.  Otherwise n < kTileAverage E; m positions of an expert
+// in l buckets make at most (m + 15 l) / 128 + 7 / 8 register chunks, n / 128 +
+// 1.9 E + 1 slots in all, below 8 E, and tile chunks are used only if they are
+// fewer.  With n < 8 E, an expert has at most a chunk per position.
 int chunk_room(int n, int nb) { return (nb < n ? nb : n) + (n + 255) / 256; }
 
 // The shared expert is one bucket of T positions, on the tile GEMM from here
@@ -898,6 +936,9 @@ void shared_plan(int T, int d, int shared_d_ff, int* cs, int* ksplit) {
   const int most = steps2 / 16 > 1 ? steps2 / 16 : 1;
   *ksplit = sp < 1 ? 1 : (sp > most ? most : sp);
 }
+
+// Weight-row tiles of W1/W3 per chunk, in both GEMMs.
+int row_tiles13(int d_ff) { return (d_ff + kTileRows / 2 - 1) / (kTileRows / 2); }
 
 // n_ub: chunks of `wk` (a bound when it is the device's table).
 template <int G, bool SWIGLU>
@@ -1022,7 +1063,7 @@ hipError_t side_stream(SideStream** out) {
 // the copy of the next unit overlaps the computation of this one.  The
 // per-position arithmetic is that of the grouped GEMM path of
 // launch_forward (how positions are grouped into blocks and chunks does not
-// change a position's sums; which GEMM an expert takes does).
+// change a position's sums; which GEMM the layer takes does).
 hipError_t launch_forward_streamed(const void* x, d2moe_dtype xd, int T, int d, int d_ff, int E,
                                    int k, const d2moe_mwq* hw13, const d2moe_mwq* hw2,
                                    const d2moe_mwq* w13, const d2moe_mwq* w2, uint8_t* resident,
@@ -1058,21 +1099,14 @@ hipError_t launch_forward_streamed(const void* x, d2moe_dtype xd, int T, int d, 
   off[0] = 0;
   for (int i = 0; i < E * Lv; ++i) off[i + 1] = off[i] + hist_host[i];
   const MwqView W13 = view_of(w13), W2 = view_of(w2);
-  // the same GEMM for an expert, and the same split of W2, as in
-  // launch_forward, so that a position's sums are the same bit for bit
+  // the same GEMM, and the same split of W2, as in launch_forward, so that a
+  // position's sums are the same bit for bit
   int32_t* table = (int32_t*)(base + L.sched_off);
-  const bool all_tile = (long)T * k >= (long)kTileAverage * E;
   const int n_chunks = chunk_estimate(T, k, E);
-  bool tile[64];
-  for (int e = 0; e < E; ++e) {
-    int blocks = 0, tiles = 0;
-    for (int l = 0; l < Lv; ++l) {
-      const int n = hist_host[e * Lv + l];
-      blocks += (n + kBlockPos - 1) / kBlockPos;
-      tiles += (n + kTileChunk - 1) / kTileChunk;
-    }
-    tile[e] = all_tile || on_tiles(tiles, (blocks + kBlocks - 1) / kBlocks);
-  }
+  ChunkCount sum{};
+  for (int e = 0; e < E; ++e) expert_blocks(hist_host + e * Lv, Lv, b_min, &sum);
+  const bool tile =
+      (long)T * k >= (long)kTileAverage * E || use_tiles(sum, row_tiles13(d_ff), T, k);
   const uint8_t *host13[3], *host2[3];
   const bool by_kernel = delta_addresses(hw13, w13, host13) && delta_addresses(hw2, w2, host2);
   for (int i = 0; i < n_units; ++i) {
@@ -1093,7 +1127,7 @@ hipError_t launch_forward_streamed(const void* x, d2moe_dtype xd, int T, int d, 
     if (resident[u.expert] < u.load_to) resident[u.expert] = (uint8_t)u.load_to;
     if (u.count <= 0) continue;
     const int first = off[u.expert * Lv + (u.bits - b_min)];
-    if (tile[u.expert]) {
+    if (tile) {
       err = launch_tile_bucket(xb, r->perm, k, w13, w2, first, u.count, u.bits, u.expert, table, h,
                                y, s);
       if (err != hipSuccess) return err;
@@ -1188,24 +1222,21 @@ hipError_t launch_forward(const void* x, d2moe_dtype xd, int T, int d, int d_ff,
     constexpr int kPer = kChunkThreads * kConvert;
     const unsigned conv = convert && !has_shared ? (unsigned)((n + kPer - 1) / kPer) : 0;
     chunk_kernel<<<1 + conv, kChunkThreads, 0, s>>>(r->hist, r->offsets, E, Lv, w13->b_min,
-                                                    L.chunk_n, all_tile, table, (const float*)x, n,
-                                                    xw);
+                                                    row_tiles13(d_ff), T, k, all_tile,
+                                                    table, (const float*)x, n, xw);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     const int n_ub = all_tile ? 0 : chunk_bound(T * k, Lv, E);
-    // an expert holds at most T positions, one per token
-    const int nt_ub =
-        all_tile ? L.chunk_n - 1 : T > kBlocks * kBlockPos ? tile_bound(T * k, Lv, E) : 0;
+    const int nt_ub = all_tile ? L.chunk_n - 1 : tile_bound(T, k, n_ub);
     const int n_chunks = chunk_estimate(T, k, E);
     const GemmWork wk{table, r->hist, r->offsets, Lv, 0, 0, 0, 0, 0};
-    const int32_t* tiles = table + 4 * (size_t)(L.chunk_n - 1);
     if (events && (err = hipEventRecord(events[0], s)) != hipSuccess) return err;
-    err = launch_tile_gemm13(xb, r->perm, k, w13, table + 1, tiles, nt_ub, h, s);
+    err = launch_tile_gemm13(xb, r->perm, k, w13, table + 1, table + 4, nt_ub, h, s);
     if (err != hipSuccess) return err;
     err = run_gemm<true>(xb, d, r->perm, k, view_of(w13), wk, n_ub, n_chunks, h, d_ff, s);
     if (err != hipSuccess) return err;
     if (events && (err = hipEventRecord(events[1], s)) != hipSuccess) return err;
     if (events && (err = hipEventRecord(events[2], s)) != hipSuccess) return err;
-    err = launch_tile_gemm2(h, w2, table + 1, tiles, nt_ub, y, s);
+    err = launch_tile_gemm2(h, w2, table + 1, table + 4, nt_ub, y, s);
     if (err != hipSuccess) return err;
     err = run_gemm<false>(h, d_ff, nullptr, 1, view_of(w2), wk, n_ub, n_chunks, y, d, s);
     if (err != hipSuccess) return err;

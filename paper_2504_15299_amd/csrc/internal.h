@@ -100,14 +100,14 @@ hipError_t launch_decode_ffn(const void* x, d2moe_dtype xd, int T, int d, int d_
                              const d2moe_mwq* w13, const d2moe_mwq* w2, const d2moe_routing* r,
                              const DecodeBuffers& b, hipStream_t s, const hipEvent_t* events);
 // The LDS-tile grouped GEMM (ffn_tile.hip): h = silu(W1 x) * (W3 x) and y = W2 h
-// over *count chunks (device, at most n_ub) of four words each, first
-// position, positions, bit-width, expert: chunk c at `last` - 4 c.
+// over *count chunks (device, at most n_ub) of four words each at `chunks`:
+// first position, positions, bit-width, expert.
 constexpr int kTileChunk = 256;  // positions per chunk
 hipError_t launch_tile_gemm13(const uint16_t* x, const int32_t* perm, int k, const d2moe_mwq* w13,
-                              const int32_t* count, const int32_t* last, int n_ub, uint16_t* h,
+                              const int32_t* count, const int32_t* chunks, int n_ub, uint16_t* h,
                               hipStream_t s);
 hipError_t launch_tile_gemm2(const uint16_t* h, const d2moe_mwq* w2, const int32_t* count,
-                             const int32_t* last, int n_ub, float* y, hipStream_t s);
+                             const int32_t* chunks, int n_ub, float* y, hipStream_t s);
 // One (expert, bit-width) bucket on it, its chunk table written to `chunks`.
 hipError_t launch_tile_bucket(const uint16_t* x, const int32_t* perm, int k, const d2moe_mwq* w13,
                               const d2moe_mwq* w2, int first, int cnt, int bits, int expert,

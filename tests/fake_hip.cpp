@@ -67,6 +67,16 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
   put("wait", s, e);
   return hipSuccess;
 }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+  static uintptr_t next = 50;
+  *s = (hipStream_t)next++;
+  return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
+  static uintptr_t next = 500;
+  *e = (hipEvent_t)next++;
+  return hipSuccess;
+}
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipGetDevice(int* d) {
   *d = 0;

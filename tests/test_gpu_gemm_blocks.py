@@ -26,9 +26,9 @@ CASES = {
     "ks2_long_reduction": (2, 8, 64, 128, 1088, {2: 20, 8: 3}),
     "two_chunks_mixed": (3, 8, 128, 256, 128, {3: 100, 5: 1, 8: 150}),
     "long_run": (8, 8, 64, 64, 64, {8: 257}),
-    # one width of more than 128 positions, and 384 positions per expert and
-    # more, take the LDS-tile GEMM (chunks of 256 positions of one width)
-    "tile_200": (2, 8, 64, 320, 64, {4: 200}),
+    "one_width_200": (2, 8, 64, 320, 64, {4: 200}),
+    # 384 positions per expert and more take the LDS-tile GEMM (chunks of 256
+    # positions of one width)
     "tile_two_widths": (5, 8, 128, 256, 128, {5: 420, 8: 1}),
     # every width on it, for each way of grouping the planes, from b_min 2 and not
     "tile_widths_from_1": (1, 8, 64, 320, 64, {b: 47 + b for b in range(1, 9)}),
