@@ -1364,15 +1364,27 @@ hipError_t launch_decode_ffn(const void* x, d2moe_dtype xd, int T, int d, int d_
   // adjacent row blocks over a quarter of the reduction (decode13_kernel, one
   // activation load for both blocks); with fewer work items (batches below
   // 8 at the Mixtral shape) the 4-wave-per-row-block kernel keeps more
-  // streams in flight and is faster.  With two or three column blocks, whose
-  // activation loads weigh more and whose waves are fewer per SIMD, pairs win
-  // from a quarter of that: one dense expert, d 5120, d_ff 13824, took 77, 94
-  // and 171 us per layer at 16, 24 and 64 tokens against 85, 106 and 195; at d
-  // 2048, 512 waves, they lose, 52 against 46.  The second block's offset is
-  // one row block of groups.
+  // streams in flight and is faster.  Pairs need fewer waves (of the bound ny)
+  // where the activation loads they share weigh more, us per layer single / pairs:
+  // * two column blocks, from 2560 (8 experts top-2, d 2048, d_ff 13824, 32 and 20
+  //   tokens 162 / 147 and 134 / 127; 2304 waves, d 1536, d_ff 8192 at 8 bits, 88.4
+  //   / 88.0; 1536, d 1024, 75 / 79), unless the pair's second block, one row block
+  //   of groups after the first, lies a multiple of 128 KiB from it (d_ff 8192 at
+  //   b_max 8: 20 tokens 88 / 90, at b_max 7 pairs gain 2.5 %);
+  // * three, nest up to 4 bits, from 1280 (one expert, d 5120, d_ff 13824, 16 tokens
+  //   85 / 79; 1024 waves, d 4096, 66 / 73);
+  // * three, wider nests, from 2048 with one expert, whose runs are all full (d 4096,
+  //   d_ff 8192, 64 tokens at 8 bits 163 / 155 at 2560 waves; 1024 91 / 94), and
+  //   from 3072 with several (8, d 2048, d_ff 8192, 64 tokens 162 / 155 at 3584
+  //   waves; 2688, d 1536, 129 / 130; 1792, d 1024, 104 / 106).
   constexpr int kW2Split = 4;
-  const bool pairs2 =
-      (d / 16) % 2 == 0 && (long)(d / 32) * ny * kW2Split >= (ncb == 1 ? 5120 : 1280);
+  const size_t pair_off = (size_t)(d_ff / G) * w2->b_max * 256;
+  const int pair_waves = ncb == 1   ? 5120
+                         : ncb == 2 ? (pair_off % (128 << 10) ? 2560 : 5120)
+                         : w2->b_max <= 4 ? 1280
+                         : E == 1         ? 2048
+                                          : 3072;
+  const bool pairs2 = (d / 16) % 2 == 0 && (long)(d / 32) * ny * kW2Split >= pair_waves;
   if (pairs2 && ncb == 1)
     err = launch_decode13_kernel<kW2Split, 1, false>(w2->b_min, ny, W2, b.elist, b.xq2, b.xs2,
                                                      npos, d, b.y, d, nullptr, s, e2, e3);

@@ -40,3 +40,23 @@ def test_a_layer_takes_one_gemm(fake, counts, bits, f, want):
     assert len(gemms) == 2 * sum(n > 0 for n in counts)
     other = "tile_gemm" if want == "bgemm" else "bgemm"
     assert all(want in op for op in gemms) and not any(other in op for op in gemms), gemms
+
+
+@pytest.mark.parametrize("E,k,T,d,f,b_max,pairs", [
+    # one column block: 5120 waves
+    (8, 2, 16, 4096, 14336, 8, True), (8, 2, 4, 4096, 14336, 8, False),
+    # two: 2560 (2816 here and 2304, 1536 below), and not over a multiple of 128 KiB
+    (8, 2, 20, 2048, 13824, 8, True), (8, 2, 20, 2048, 8192, 8, False),
+    (8, 2, 20, 2048, 8192, 7, True), (4, 2, 16, 3072, 7168, 8, False),
+    (8, 2, 32, 1024, 8192, 7, False),
+    # three: 1280 up to 4 bits, else 2048 for one expert and 3072 for several
+    (1, 1, 16, 5120, 13824, 4, True), (1, 1, 16, 5120, 13824, 8, False),
+    (1, 1, 16, 4096, 13824, 4, False), (1, 1, 64, 4096, 8192, 8, True),
+    (8, 2, 64, 2048, 8192, 8, True), (8, 2, 64, 1536, 8192, 8, False),
+])
+def test_decode_w2_takes_row_block_pairs(fake, E, k, T, d, f, b_max, pairs):
+    ops = _kernels(fake, dict(kind="forward", T=T, d=d, f=f, E=E, k=k, b_min=2, b_max=b_max,
+                              group=128))
+    # activation prep, W1/W3, prep, W2, combine
+    assert len(ops) == 5 and "decode13_kernel" in ops[1], ops
+    assert ("decode13_kernel" if pairs else "13decode_kernel") in ops[3], ops[3]
