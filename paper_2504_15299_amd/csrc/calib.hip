@@ -83,6 +83,15 @@ __device__ inline double lane_value(double v, int lane) {
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
+// Between one wave's LDS writes and other lanes' reads of them.  The hardware
+// serves a wave's LDS accesses in order; this keeps the compiler to that order and
+// costs no instruction.
+__device__ inline void wave_handoff() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // f(integral_constant<int, w>) for w = FT, FT - kPhase, .., kPhase.
 constexpr int kPhase = 16;
 template <int W = FT, typename F>
@@ -128,11 +137,10 @@ __global__ __launch_bounds__(64) void potrf_diag_kernel(double* __restrict__ A, 
       const double x = r == j ? d : v[0] / d;
       a[r][j] = r >= j ? x : 0.0;
       if (r >= j) l[r - j] = x;
-      // the only wave: its LDS accesses are served in order
-      __builtin_amdgcn_wave_barrier();
+      wave_handoff();
 #pragma unroll
       for (int i = 1; i < W; ++i) v[i - 1] = fma(-x, l[i], v[i]);
-      __builtin_amdgcn_wave_barrier();
+      wave_handoff();
     }
   });
   __syncthreads();
@@ -427,8 +435,8 @@ __global__ __launch_bounds__(64 * kQuantWaves) void calib_quant_kernel(
     for (int r = 0; r < kQuantRows; ++r)
 #pragma unroll
       for (int c = 0; c < C; ++c) mag[wave][r][64 * c + lane] = fabsf(t[r][c]);
-    // lane r NG + g sums group g of row r in ascending column order (the
-    // wave's own LDS writes above are ordered before these reads)
+    wave_handoff();
+    // lane r NG + g sums group g of row r in ascending column order
     float acc = 0.0f;
     if (lane < kQuantRows * NG) {
       const float4* src = (const float4*)&mag[wave][lane / NG][(lane % NG) * G];
