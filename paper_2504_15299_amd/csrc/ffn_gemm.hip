@@ -832,11 +832,14 @@ DeltaPart delta_part(const uint8_t* const host[3], const d2moe_mwq* dm, int e, i
   return d;
 }
 
-// Device addresses of the host copy's three arrays, if the device can read
-// them (pinned memory) and both copies allow 16-byte words.
+// Device addresses of the host copy's three arrays, if the device can read all
+// of each (within one pinned allocation: an array may go on past the end of the
+// one that its first byte lies in) and both copies allow 16-byte words.
 bool delta_addresses(const d2moe_mwq* hm, const d2moe_mwq* dm, const uint8_t* host[3]) {
   const void* const h[3] = {hm->planes, hm->scales, hm->zeros};
   const void* const d[3] = {dm->planes, dm->scales, dm->zeros};
+  const size_t values = (size_t)hm->n_experts * hm->rows * hm->cols, groups = values / hm->group;
+  const size_t bytes[3] = {values / 8 * hm->b_max, groups * (hm->b_max - hm->b_min + 1) * 2, groups};
   for (int i = 0; i < 3; ++i) {
     hipPointerAttribute_t at;
     if (hipPointerGetAttributes(&at, h[i]) != hipSuccess) {
@@ -847,6 +850,14 @@ bool delta_addresses(const d2moe_mwq* hm, const d2moe_mwq* dm, const uint8_t* ho
     const uint8_t* dev =
         (const uint8_t*)at.devicePointer + ((const uint8_t*)h[i] - (const uint8_t*)at.hostPointer);
     if ((((uintptr_t)dev | (uintptr_t)d[i]) & 15u) != 0) return false;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)dev) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    const uintptr_t at_byte = (uintptr_t)dev - (uintptr_t)base;
+    if ((uintptr_t)dev < (uintptr_t)base || at_byte > size || bytes[i] > size - at_byte) return false;
     host[i] = dev;
   }
   return true;

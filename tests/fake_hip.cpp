@@ -90,4 +90,10 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t* at, const void* p) {
   at->devicePointer = at->hostPointer = (void*)p;
   return hipSuccess;
 }
+hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* size, hipDeviceptr_t p) {
+  const uintptr_t u = (uintptr_t)p;
+  if (u < pinned_from || u >= pinned_to) return hipErrorNotFound;
+  *base = (hipDeviceptr_t)pinned_from, *size = pinned_to - pinned_from;
+  return hipSuccess;
+}
 }

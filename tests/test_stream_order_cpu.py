@@ -76,3 +76,23 @@ def test_copies_overlap_the_products_of_earlier_units(fake):
         for i, e in enumerate(log):
             if e[0] == call and "copy_delta" in e[1]:
                 assert not products & before[i]
+
+
+# Host arrays of the two matrices at the stand-in's addresses: planes, scales and
+# zero points of each 64 GiB apart; 2 experts of 128-wide matrices need 64 KiB and
+# less each.
+_LAST = 5 << 36   # offset of the last array (w2's zero points)
+
+
+@pytest.mark.parametrize("pinned,by_kernel", [
+    (_LAST + 256, True),       # exactly to the end of the last array: 2 x 128 x 1 bytes
+    (_LAST + 255, False),      # its last byte is not in the allocation
+    (_LAST + 1, False), (_LAST, False), ((2 << 36) + 512, False), (1, False)])
+def test_device_reads_host_weights_only_inside_their_allocation(fake, pinned, by_kernel):
+    """Weights whose first byte is pinned but that go on past the end of that
+    allocation are not read by the device; the runtime copies them, each
+    rectangle from wherever it lies."""
+    log = _two_calls(fake, pinned)
+    ops = {op for _, op, s, _ in log if s == IO}
+    assert any("copy_delta" in op for op in ops) == by_kernel
+    assert ("copy" in ops) == (not by_kernel)
