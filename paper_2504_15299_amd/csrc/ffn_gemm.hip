@@ -85,7 +85,7 @@ __host__ __device__ inline int expert_blocks(const int32_t* n, int L, int b_min,
   }
   const int reg = (blocks + kBlocks - 1) / kBlocks;
   c->reg += reg;
-  c->cost += reg * (24 + top + 4 * widths);
+  c->cost += reg * (24 + 3 * top + 4 * widths);
   return blocks;
 }
 
@@ -95,37 +95,43 @@ __host__ __device__ inline int expert_blocks(const int32_t* n, int L, int b_min,
 // a step took 392 us with half of them on tiles, 280 on registers, 283 on tiles).
 // A chunk dequantizes 128 rows, once for up to 256 positions of one width (tile)
 // or 128 of any (register).  A register chunk of w widths up to b bits takes
-// about (24 + b + 4 w) / 48 of a tile chunk's time; 512 workgroups run at once,
-// so fewer than that take the time of one.  Fitted to 1568 layers (E 1 to 64, d
-// 512 to 5120, 40 to 380 positions per expert, one to seven widths, even and Zipf
-// load): 0.3 % above the faster GEMM on average, tile / register, us per step: 8
-// experts of d 4096, d_ff 14336, 260 per expert, 8 bits 1651 / 2145 (tile), 4
-// bits 1368 / 1358 and widths 2, 4, 8 2207 / 2121 (register); 4 experts of d 1024,
-// d_ff 2048, 260 per expert, 4 bits 115 / 86 (register: 224 workgroups); 16 of d
-// 2048, d_ff 1408, Zipf load, 180 per expert, each of one width, 176 / 208 (tile).
+// about (24 + 3 b + 4 w) / 48 of a tile chunk's time in W1/W3, and 0.4 of that in
+// W2, whose reduction it takes in two groups where workgroups are few; about 256
+// workgroups of W1/W3 and 384 of W2 run at once, so fewer take the time of that
+// many.  Fitted to 1828 layers (E 1 to 64, d 512 to 5120, up to 384 positions per
+// expert, one to seven widths, even and Zipf load): 0.2 % above the faster GEMM on
+// average.  Tile / register, us per step: 8 experts of d 4096, d_ff 14336, 260 per
+// expert, 8 bits 1651 / 2145 (tile), 4 bits 1368 / 1358 and widths 2, 4, 8 2207 /
+// 2121 (register); 4 experts of d 1024, d_ff 2048, 260 per expert, 4 bits 115 / 86
+// (register: 224 workgroups); 16 of d 2048, d_ff 1408, Zipf load, 180 per expert,
+// each of one width, 176 / 208 (tile).
 // From kTileAverage positions per expert on it is tiles whatever the counts, so
 // that the register launch is left out.
 constexpr int kTileAverage = 384;
 // Bound on the tile chunks of a layer of T tokens, top-k, that would make at most
-// `reg` register chunks; at 0 the tile launch is left out.  use_tiles keeps to it,
-// which excludes nothing that the costs favour: with at most 128 tokens, and so
-// positions per expert, there are no fewer tile chunks than register chunks, and
-// the costs need 30 positions or more per tile chunk.
+// `reg` register chunks; at 0 the tile launch is left out.  use_tiles keeps to it:
+// as many tile chunks as register chunks are slower (with at most 128 tokens, and
+// so positions per expert, there are no fewer), and so are tile chunks of few
+// positions (64 experts, Zipf load, 45 per tile chunk 343 / 247).
 __host__ __device__ inline int tile_bound(int T, int k, int reg) {
   if (T <= kBlocks * kBlockPos) return 0;
-  return T * k / 29 < reg ? T * k / 29 : reg - 1;
+  return T * k / 48 < reg ? T * k / 48 : reg - 1;
 }
-__host__ __device__ inline bool use_tiles(const ChunkCount& c, int row_tiles, int T, int k) {
+__host__ __device__ inline bool use_tiles(const ChunkCount& c, int T, int k, int d, int d_ff) {
   if (c.tiles > tile_bound(T, k, c.reg)) return false;
-  const long reg = (long)c.reg * row_tiles, tiles = (long)c.tiles * row_tiles;
-  return c.cost * (reg > 512 ? reg : 512) > 48l * c.reg * (tiles > 512 ? tiles : 512);
+  const long rows13 = (d_ff + kTileRows / 2 - 1) / (kTileRows / 2);
+  const long rows2 = (d + kTileRows - 1) / kTileRows;
+  auto at_least = [](long n, long least) { return n > least ? n : least; };
+  const long reg = 5 * at_least(c.reg * rows13, 256) * d + 2 * at_least(c.reg * rows2, 384) * d_ff;
+  const long tiles = 5 * (at_least(c.tiles * rows13, 256) * d + at_least(c.tiles * rows2, 384) * d_ff);
+  return c.cost * reg > 48 * c.reg * tiles;
 }
 
 // Chunk table of the layer's GEMM from the routing histogram, in slots of four
 // words: slot 0 = {register chunks, tile chunks}, one of them 0; then the chunks,
 // a register chunk as {expert | blocks << 8, first block of the expert} (an
 // expert's chunks are of even size), a tile chunk as {first position, positions,
-// bit-width, expert}.  row_tiles: workgroups of W1/W3 per chunk.
+// bit-width, expert}.
 //
 // Longest workgroups first: experts (buckets) of the largest bit-width, then of
 // the most positions.  One workgroup of kChunkThreads threads, one per expert
@@ -136,7 +142,7 @@ constexpr int kChunkThreads = 512;
 constexpr int kConvert = 4;  // values per thread
 __global__ __launch_bounds__(kChunkThreads) void chunk_kernel(
     const int32_t* __restrict__ hist, const int32_t* __restrict__ offsets, int E, int L, int b_min,
-    int row_tiles, int T, int k, bool all_tile, int32_t* __restrict__ table,
+    int T, int k, int d, int d_ff, bool all_tile, int32_t* __restrict__ table,
     const float* __restrict__ x, size_t n, uint16_t* __restrict__ xb) {
   if (blockIdx.x > 0) {  // workgroup-uniform
     const size_t i0 = (size_t)(blockIdx.x - 1) * (kChunkThreads * kConvert) + threadIdx.x;
@@ -147,37 +153,38 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_kernel(
     }
     return;
   }
-  __shared__ int rkey[64];
-  __shared__ ChunkCount count[64];
+  __shared__ int rkey[64], nreg[64];
+  __shared__ ChunkCount total;
   __shared__ int tkey[kChunkThreads], ntile[kChunkThreads];
   const int j = threadIdx.x;
   int tot = 0;
-  if (j < E) {
+  if (j < 64) {  // the first wave
     int n[8], mb = 0;
 #pragma unroll
     for (int l = 0; l < 8; ++l) {
-      n[l] = l < L ? hist[j * L + l] : 0;
+      n[l] = j < E && l < L ? hist[j * L + l] : 0;
       if (n[l] > 0) mb = l + 1;
     }
     ChunkCount c{};
     tot = expert_blocks(n, 8, b_min, &c);
-    count[j] = c;
     rkey[j] = (mb << 24) + min(tot, (1 << 24) - 1);
+    nreg[j] = c.reg;
+    for (int off = 32; off > 0; off >>= 1)
+      c.add({__shfl_xor(c.reg, off, 64), __shfl_xor(c.cost, off, 64), __shfl_xor(c.tiles, off, 64)});
+    if (j == 0) total = c;
   }
   __syncthreads();
-  ChunkCount sum{};
+  const ChunkCount sum = total;
   int first = 0;
-  for (int o = 0; o < E; ++o) {
-    sum.add(count[o]);
-    if (j < E && (rkey[o] > rkey[j] || (rkey[o] == rkey[j] && o < j))) first += count[o].reg;
-  }
-  if (!all_tile && !use_tiles(sum, row_tiles, T, k)) {  // workgroup-uniform
+  if (!all_tile && !use_tiles(sum, T, k, d, d_ff)) {  // workgroup-uniform
     if (j == 0) {
       table[0] = sum.reg;
       table[1] = 0;
     }
     if (j < E) {
-      const int nc = count[j].reg;
+      for (int o = 0; o < E; ++o)
+        if (rkey[o] > rkey[j] || (rkey[o] == rkey[j] && o < j)) first += nreg[o];
+      const int nc = nreg[j];
       for (int c = 0; c < nc; ++c) {
         const int b0 = (int)((long)c * tot / nc), b1 = (int)((long)(c + 1) * tot / nc);
         table[4 * (1 + first + c)] = j | (b1 - b0) << 8;
@@ -191,7 +198,6 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_kernel(
   ntile[j] = (cnt + kTileChunk - 1) / kTileChunk;
   tkey[j] = cnt > 0 ? ((j % L + 1) << 24) + min(cnt, (1 << 24) - 1) : 0;
   __syncthreads();
-  first = 0;
   for (int o = 0; o < nb; ++o)
     if (tkey[o] > tkey[j] || (tkey[o] == tkey[j] && o < j)) first += ntile[o];
   if (j == 0) {
@@ -948,9 +954,6 @@ void shared_plan(int T, int d, int shared_d_ff, int* cs, int* ksplit) {
   *ksplit = sp < 1 ? 1 : (sp > most ? most : sp);
 }
 
-// Weight-row tiles of W1/W3 per chunk, in both GEMMs.
-int row_tiles13(int d_ff) { return (d_ff + kTileRows / 2 - 1) / (kTileRows / 2); }
-
 // n_ub: chunks of `wk` (a bound when it is the device's table).
 template <int G, bool SWIGLU>
 hipError_t run_gemm_g(const uint16_t* in, int in_ld, const int32_t* perm, int kdiv,
@@ -1116,8 +1119,7 @@ hipError_t launch_forward_streamed(const void* x, d2moe_dtype xd, int T, int d, 
   const int n_chunks = chunk_estimate(T, k, E);
   ChunkCount sum{};
   for (int e = 0; e < E; ++e) expert_blocks(hist_host + e * Lv, Lv, b_min, &sum);
-  const bool tile =
-      (long)T * k >= (long)kTileAverage * E || use_tiles(sum, row_tiles13(d_ff), T, k);
+  const bool tile = (long)T * k >= (long)kTileAverage * E || use_tiles(sum, T, k, d, d_ff);
   const uint8_t *host13[3], *host2[3];
   const bool by_kernel = delta_addresses(hw13, w13, host13) && delta_addresses(hw2, w2, host2);
   for (int i = 0; i < n_units; ++i) {
@@ -1233,8 +1235,8 @@ hipError_t launch_forward(const void* x, d2moe_dtype xd, int T, int d, int d_ff,
     constexpr int kPer = kChunkThreads * kConvert;
     const unsigned conv = convert && !has_shared ? (unsigned)((n + kPer - 1) / kPer) : 0;
     chunk_kernel<<<1 + conv, kChunkThreads, 0, s>>>(r->hist, r->offsets, E, Lv, w13->b_min,
-                                                    row_tiles13(d_ff), T, k, all_tile,
-                                                    table, (const float*)x, n, xw);
+                                                    T, k, d, d_ff, all_tile, table,
+                                                    (const float*)x, n, xw);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     const int n_ub = all_tile ? 0 : chunk_bound(T * k, Lv, E);
     const int nt_ub = all_tile ? L.chunk_n - 1 : tile_bound(T, k, n_ub);

@@ -25,7 +25,7 @@ def fake(tmp_path_factory):
 
 
 def _spec(**kw):
-    c = dict(d=128, f=2752, E=8, k=1, T=2000, group=64, x_dtype="bf16", n_requests=1, shared_f=0)
+    c = dict(d=2048, f=768, E=16, k=2, T=1200, group=64, x_dtype="bf16", n_requests=1, shared_f=0)
     c.update(kw)
     return wl.scaled(wl.tiny(seed=41), **c)
 
@@ -38,8 +38,11 @@ def _gemms(fake, s, **kw):
 
 
 def _check(L, got):
+    """Every 17th token that is not ambiguous against the oracle."""
     amb = ambiguous_tokens(L.ref_logits, L.spec.k, logit_error_bound(L.x, L.Wg, L.bias))
-    err = row_max_abs_rel(got, L.reference())[~amb]
+    tokens = [t for t in range(0, L.spec.T, 17) if not amb[t]]
+    ref = L.reference(tokens=tokens)
+    err = row_max_abs_rel(got[tokens], ref)
     assert np.isfinite(got).all() and err.max() <= FWD_TOL, err.max()
 
 
@@ -51,14 +54,14 @@ def _pinned(m):
 
 # name: (spec, widths of the experts, the GEMM that the layer takes)
 CASES = {
-    "tile_8_bits": (dict(), [8] * 8, "tile_gemm"),
-    "tile_zipf": (dict(k=2, T=1400, zipf_s=1.1), [8, 8, 4, 4, 8, 2, 2, 3], "tile_gemm"),
-    "tile_two_widths": (dict(T=2600, n_requests=2, E=8), [[4] * 8, [2] * 8], "tile_gemm"),
-    "tile_group_128": (dict(group=128, f=2816), [8, 7, 6, 5, 8, 7, 6, 5], "tile_gemm"),
+    "tile_8_bits": (dict(), [8] * 16, "tile_gemm"),
+    "tile_zipf": (dict(T=1400, zipf_s=1.1), [8, 8, 4, 4, 8, 2, 2, 3] * 2, "tile_gemm"),
+    "tile_two_widths": (dict(T=2400, n_requests=2), [[8] * 16, [4] * 16], "tile_gemm"),
+    "tile_group_128": (dict(group=128), [8, 7, 6, 5] * 4, "tile_gemm"),
     # the same loads in a layer of few workgroups, and loads of which some
     # experts alone would take the tile GEMM
-    "register_small_layer": (dict(f=128, d=192), [8] * 8, "bgemm"),
-    "register_zipf": (dict(k=2, T=700, zipf_s=1.1, f=320), [2, 3, 4, 8, 2, 3, 4, 8], "bgemm"),
+    "register_small_layer": (dict(f=128, d=192), [8] * 16, "bgemm"),
+    "register_zipf": (dict(T=700, zipf_s=1.1, d=192, f=320), [2, 3, 4, 8] * 4, "bgemm"),
 }
 
 
