@@ -2,7 +2,7 @@
 // error ||WX - W^X||^2 over calibration activations X; Algorithm 1 quantizes
 // the weights block by block and moves each block's quantization error onto
 // the columns not yet quantized through H^c, the Cholesky factor of the
-// inverse of H = 2 X X^T + lambda I).  Setup work, not on the timed path.
+// inverse of H = 2 X X^T + lambda I).  Setup work, once per model.
 //
 // Factor (binary64): U = upper-triangular factor with H^-1 = U^T U.  With J
 // the order-reversing permutation, J H J = L L^T (lower Cholesky factor L)

@@ -24,8 +24,8 @@ def _snapshot(r: api.Routing, out):
 GRAPH_SPECS = {
     "decode_T4": wl.scaled(wl.mixtral_decode(T=4), d=512, f=384),
     "decode_T16": wl.scaled(wl.mixtral_decode(T=16), d=512, f=384),
-    # the grouped-GEMM path: chunk tables built on the device, wide and narrow
-    # chunks, and a shared expert whose W2 reduction is split in parts
+    # the grouped-GEMM path: the chunk table built on the device, and a shared
+    # expert whose W2 reduction is split in parts
     "prefill_small": wl.scaled(wl.mixtral_prefill(), d=256, f=384, T=600),
     "fine_shared_split": wl.scaled(wl.fine_grained(), d=256, f=64, T=200, shared_f=1024),
 }

@@ -1,5 +1,5 @@
-"""The forward runs the shared expert and the small routed experts on side
-streams of the calling host thread.  Two host threads, each on its own stream
+"""The forward runs the shared expert on a side stream of the calling host
+thread.  Two host threads, each on its own stream
 with its own buffers, run the same layers at the same time and must reproduce
 the single-thread outputs bit for bit (the kernels are deterministic), and a
 layer on the default stream must as well."""
