@@ -299,27 +299,33 @@ __global__ __launch_bounds__(kHistThreads) void hist_perm_kernel(
   for (int s = tid; s < n; s += kHistThreads)
     atomicAdd(&cnt[inline_keys ? lkey[s] : topk_idx[s] * L + (topk_bits[s] - b_min)], 1);
   __syncthreads();
-  // exclusive scan by the first wave, nkeys / 64 keys per lane (one thread
-  // walking 448 keys in LDS took about 5 us)
+  // exclusive scan by the first wave, as few keys per lane as hold them, the
+  // lanes' sums by DPP row shifts (one thread walking 448 keys in LDS took about 5
+  // us; eight keys per lane and shuffles through the LDS path took 0.3 to 0.45 us
+  // longer than that thread at 7 to 48 keys)
   if (wave == 0) {
     constexpr int kPer = kMaxKeys / 64;
+    const int per = (nkeys + 63) / 64;  // uniform
     int v[kPer], sum = 0;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
-      const int j = lane * kPer + q;
-      v[q] = j < nkeys ? cnt[j] : 0;
+      const int j = lane * per + q;
+      v[q] = q < per && j < nkeys ? cnt[j] : 0;
       sum += v[q];
     }
-    int inc = sum;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int u = __shfl_up(inc, o, 64);
-      if (lane >= o) inc += u;
-    }
+    int inc = sum;  // within the row of 16 lanes, then across the rows
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x111, 0xf, 0xf, true);
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x112, 0xf, 0xf, true);
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xf, 0xf, true);
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x118, 0xf, 0xf, true);
+    const int r0 = __builtin_amdgcn_readlane(inc, 15), r1 = __builtin_amdgcn_readlane(inc, 31),
+              r2 = __builtin_amdgcn_readlane(inc, 47);
+    inc += lane < 16 ? 0 : lane < 32 ? r0 : lane < 48 ? r0 + r1 : r0 + r1 + r2;
     int acc = inc - sum;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
-      const int j = lane * kPer + q;
-      if (j < nkeys) off[j] = acc;
+      const int j = lane * per + q;
+      if (q < per && j < nkeys) off[j] = acc;
       acc += v[q];
     }
     if (lane == 63) off[nkeys] = acc;
