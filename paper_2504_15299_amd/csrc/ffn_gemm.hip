@@ -74,9 +74,6 @@ struct GemmWork {
 // bucket in chunks of kTileChunk.
 struct ChunkCount {
   int reg, cost, tiles;  // cost: of the register chunks (use_tiles)
-  __host__ __device__ void add(const ChunkCount& o) {
-    reg += o.reg, cost += o.cost, tiles += o.tiles;
-  }
 };
 __host__ __device__ inline int expert_blocks(const int32_t* n, int L, int b_min, ChunkCount* c) {
   int blocks = 0, widths = 0, top = 0;
@@ -130,6 +127,16 @@ __host__ __device__ inline bool use_tiles(const ChunkCount& c, int T, int k, int
   return c.cost * reg > 48 * c.reg * tiles;
 }
 
+// Sum over the 64 lanes of a wave, in every lane (DPP row shifts, then the rows).
+__device__ inline int wave_total(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+  return __builtin_amdgcn_readlane(v, 15) + __builtin_amdgcn_readlane(v, 31) +
+         __builtin_amdgcn_readlane(v, 47) + __builtin_amdgcn_readlane(v, 63);
+}
+
 // Chunk table of the layer's GEMM from the routing histogram, in slots of four
 // words: slot 0 = {register chunks, tile chunks}, one of them 0; then the chunks,
 // a register chunk as {expert | blocks << 8, first block of the expert} (an
@@ -172,8 +179,7 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_kernel(
     tot = expert_blocks(n, 8, b_min, &c);
     rkey[j] = (mb << 24) + min(tot, (1 << 24) - 1);
     nreg[j] = c.reg;
-    for (int off = 32; off > 0; off >>= 1)
-      c.add({__shfl_xor(c.reg, off, 64), __shfl_xor(c.cost, off, 64), __shfl_xor(c.tiles, off, 64)});
+    c = {wave_total(c.reg), wave_total(c.cost), wave_total(c.tiles)};
     if (j == 0) total = c;
   }
   __syncthreads();
